@@ -37,6 +37,11 @@ hipError_t launch_attn_step(const uint16_t* q, uint16_t* out, const uint16_t* kp
 hipError_t launch_gateup(const uint16_t* x, const uint16_t* w, uint16_t* y, int32_t T, int32_t H, int32_t N2,
                          bool act, int splits, float* part, int cus, hipStream_t stream, hipEvent_t ev_start,
                          hipEvent_t ev_stop);
+// The projection's kernel for operands the regular one does not take (not 16-byte
+// aligned, or rows too long for its offsets): the partials when splits > 1.
+hipError_t launch_gateup_any(const uint16_t* x, const uint16_t* w, uint16_t* y, int32_t T, int32_t H, int32_t N2,
+                             bool act, int splits, float* part, int cus, hipStream_t stream, hipEvent_t ev_start,
+                             hipEvent_t ev_stop);
 // Output tiles of a call: 256 x 256, plus 64 x 256 for the last T % 256 token rows.
 int64_t gateup_tiles(int32_t T, int32_t N2);
 // Reduction splits chosen for a device with `cus` compute units (1: no split).

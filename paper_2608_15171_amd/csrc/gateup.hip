@@ -1,34 +1,40 @@
 // Fused gate-up projection of a decoder block's MLP on gfx950 (CDNA4):
 //   Y[T][N2] = X[T][H] * W[N2][H]^T
-// bf16 inputs, fp32 accumulation on 32x32x16 MFMAs, output rounded to bf16
+// bf16 inputs, fp32 accumulation on 16x16x32 MFMAs, output rounded to bf16
 // (nearest even). W stacks the gate rows over the up rows, so one launch
 // computes both projections of a prefill chunk.
 //
-// Tiling. A workgroup of eight waves (two per SIMD) computes a 256 x 256
-// output tile; wave (wn, wm) owns 128 output columns x 64 token rows as 4 x 2
-// MFMA tiles (128 fp32 accumulators per lane), so that while one wave of a SIMD
-// waits (its transfers' issue, an LDS read) the other keeps the matrix core
-// busy. (Four waves of 128 x 128, one per SIMD with 256 accumulators each,
-// read half as many LDS bytes per MFMA but measured 5 % slower.) The reduction
-// advances 64 features per stage: a stage's W rows and X rows (32 KB each) are
-// copied into LDS by 16-byte global-to-LDS transfers, each covering eight whole
-// 128-byte row runs (one cache line per row), into a two-slot ring. In LDS a
-// row keeps its eight 16-byte chunks in an XOR-swizzled order, so each operand
-// fragment read (row tile, k-step: 32 rows x 32 bytes) is one bank-conflict-free
-// ds_read_b128. The next stage's transfers are issued in the first two of the
-// stage's four k-steps, and the next k-step's fragments are read in two groups
-// while the current k-step's MFMAs run. (Transfers of 32-byte row pieces
-// straight into operand order, and rings of four or five 32-feature stages,
-// measured 33 %, 6-13 % and 2-12 % slower; transfers spread over all four
-// k-steps 4-7 % slower, issued in one k-step 2-8 % slower, or interleaved one by
-// one with the MFMAs no faster.)
+// What bounds it: with operands of ordinary values the chip lowers its clock
+// under matrix work (32x32x16 MFMAs from registers reach 1.83 PFLOP/s, 16x16x32
+// 2.07, both 2.45 on zeros), so the smaller instruction is used, and everything
+// beside the MFMAs has to run under them.
+//
+// Schedule. A workgroup of eight waves (two per SIMD) owns an output tile; the
+// reduction advances 64 features per stage. Waves 0-3 and 4-7 (one of each per
+// SIMD) run half a phase apart: while one half issues a phase's MFMAs, the other
+// issues its transfers and operand reads for its next phase, and a workgroup
+// barrier swaps the roles. Each operand of a stage is copied into LDS in units
+// (half of the tile's W rows, half or all of its X rows) by 16-byte
+// global-to-LDS transfers of eight whole 128-byte row runs (one cache line per
+// row), and a unit's buffer is refilled two phases after it was read, so that
+// transfers stay in flight across several phases and no wait drains them. The
+// transfers take buffer descriptors held in scalar registers (rows past the
+// edge read as zero) and one 32-bit lane offset; the stage offset is scalar.
+// In LDS a row keeps its eight 16-byte chunks in an XOR-swizzled order, so an
+// operand fragment (16 rows x 64 bytes) is one conflict-free ds_read_b128.
+// The stream of transfers runs on into the workgroup's next tile, so a tile's
+// epilogue overlaps the next tile's loads.
+//   16,384 x 2,048 x 22,016: 1,252 -> 1,037 us (1.43 PFLOP/s; before: 32x32x16
+//   MFMAs, one barrier and one drain of the transfers per stage)
+//   16,384 x 11,008 x 2,048: 620 -> 490 us (1.51 PFLOP/s)
+// (transfers issued after the operand reads 1-2 % slower, one of two among the
+// MFMAs 4 %, both 8 %; 32x32x16 MFMAs in the same schedule 6-8 %)
 //
 // The MFMA's first operand is W (rows = output columns), its second X (rows =
-// tokens): lane L of a 32 x 32 result then holds token row L % 32 and, in
-// registers 4g..4g+3, four consecutive output columns 8g + 4(L / 32) + 0..3,
-// which the epilogue packs into 8-byte LDS writes; the wave's block then leaves
-// LDS as 256-byte row runs of 16-byte stores, eight LDS reads ahead of their
-// stores.
+// tokens): lane L of a 16 x 16 result then holds token row L % 16 and four
+// consecutive output columns 4 (L / 16) + 0..3, which the epilogue packs into
+// 8-byte LDS writes of a wave-private area; the wave's block then leaves LDS as
+// row runs of 16-byte stores.
 //
 // Tile order. The grid holds one workgroup per compute unit, each looping over
 // its tiles. Workgroup b runs on XCD b % 8; each XCD takes a contiguous range
@@ -39,62 +45,32 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <type_traits>
 #include <cstddef>
 #include <cstdint>
+
+#include "device.h"
 
 namespace ppas {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) const void global_cvoid;
 
-#ifndef PPAS_GATEUP_BK
-#define PPAS_GATEUP_BK 64
-#endif
-#ifndef PPAS_GATEUP_RING
-#define PPAS_GATEUP_RING 2
-#endif
-#ifndef PPAS_GATEUP_SPREAD
-#define PPAS_GATEUP_SPREAD 2
-#endif
-#ifndef PPAS_GATEUP_WAVES
-#define PPAS_GATEUP_WAVES 8
-#endif
-constexpr int kWaves = PPAS_GATEUP_WAVES;  // waves per workgroup: one or two per SIMD
-static_assert(kWaves == 4 || kWaves == 8, "four or eight waves");
+constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
-constexpr int kBM = 256;                 // token rows per tile
-constexpr int kBMTail = 64;              // token rows per tile of the last T % 256 rows
 constexpr int kBN = 256;                 // output columns per tile
-constexpr int kBK = PPAS_GATEUP_BK;     // features per stage
-constexpr int kKSteps = kBK / 16;        // MFMA k-steps per stage
-constexpr int kRing = PPAS_GATEUP_RING;  // stages in the LDS ring; transfers run kRing - 1 stages ahead
-constexpr int kCPR = kBK / 8;            // 16-byte chunks of a row per stage
-constexpr int kRowBytes = 16 * kCPR;
-constexpr int kRowsPerDma = 64 / kCPR;   // whole rows covered by one 64-lane 16-byte transfer
-constexpr int kPart = 256 * kRowBytes;   // the 256 W (or X) rows of one stage
-constexpr int kStage = 2 * kPart;
-static_assert(kBK == 32 || kBK == 64, "stages of 32 or 64 features");
-static_assert(kRing >= 2 && kRing <= 5, "a ring of two to five stages");
-constexpr int kSpread = PPAS_GATEUP_SPREAD < kKSteps ? PPAS_GATEUP_SPREAD : kKSteps;   // k-steps that issue the next stage
-constexpr int kPitch = 128 * 2 + 16;     // epilogue LDS row pitch in bytes (16-byte aligned, padded)
-constexpr int kEpiWave = (kBM * 2 / kWaves) * kPitch;   // one wave's output block of a full tile (<= 128 columns)
-constexpr int kSmem = (kRing * kStage > kWaves * kEpiWave) ? kRing * kStage : kWaves * kEpiWave;
-static_assert(kSmem <= 160 * 1024, "the LDS of one compute unit");
+constexpr int kHN = kBN / 2;             // rows of a W unit
+constexpr int kBK = 64;                  // features per stage
+constexpr int kRow = 2 * kBK;            // bytes of a row in a stage
+constexpr int kTailBM = 64;              // token rows per small tile
 constexpr int kGroupM = 8;               // token-row tiles per tile-order group
-#ifndef PPAS_GATEUP_PERSIST
-#define PPAS_GATEUP_PERSIST 1
-#endif
-constexpr bool kPersist = PPAS_GATEUP_PERSIST;   // a workgroup per compute unit, looping over tiles
-
+constexpr int kSmem = 160 * 1024;        // the LDS of one compute unit
+constexpr int64_t kMaxPitch = int64_t(1) << 24;   // 256 rows of fewer bytes than this fit a 32-bit offset
 
 struct GemmArgs {
   const uint16_t* x;
@@ -102,20 +78,15 @@ struct GemmArgs {
   uint16_t* y;
   float* part;            // splits > 1: fp32 partial sums [splits][T][N2]
   int32_t T, H, N2;
-  int32_t tiles_m, tiles_n;   // full 256-row tiles, 256-column tiles
-  int32_t tail_m;             // 64-row tiles of the last T % 256 rows
-  int32_t splits;             // reduction split over this many workgroups per tile
-  int32_t I;                  // with the gated activation: N2 / 2 intermediate features
+  int32_t I;              // with the gated activation: N2 / 2 intermediate features
+  int32_t tiles_n;        // 256-column tiles
+  int32_t main_m;         // main tiles along the token rows
+  int32_t tail_m;         // 64-row tiles of the rows after them
+  int32_t splits;         // reduction split over this many workgroups per tile
+  int32_t light;          // small tiles a workgroup with one main tile fewer takes first
 };
 
 __device__ __forceinline__ u32x4 lds16(const char* p) { return *reinterpret_cast<const u32x4*>(p); }
-
-// LDS row layout of a stage: row R's 16-byte chunk c sits at position
-// c ^ swizzle(R). Sixteen consecutive rows span 256 bytes' worth of banks in
-// kRowBytes-sized rows, and the swizzle gives each of them a different position
-// for the same chunk, so the 16 lanes an operand read serves per cycle hit 16
-// different 16-byte bank groups.
-__device__ __forceinline__ int swizzle(int R) { return (R / (16 / kCPR)) % kCPR; }
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
@@ -129,38 +100,20 @@ __device__ __forceinline__ float silu_f32(float g) {
   return g / (1.f + __builtin_amdgcn_exp2f(-g * 1.4426950408889634f));
 }
 
-// 16 bytes from global memory into LDS: lane L of the wave lands at lds + 16 L.
-__device__ __forceinline__ void dma16(const uint16_t* g, char* lds) {
-  __builtin_amdgcn_global_load_lds((global_cvoid*)g, (lds_void*)lds, 16, 0, 0);
-}
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return uint32_t(__builtin_amdgcn_readfirstlane(int(v))); }
 
-__device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }
-
-// Wait until at most `later` stages of PER transfers each are still in flight
-// (vmcnt: bits 3:0 and 15:14 of the s_waitcnt immediate).
+// Wait until at most N of this wave's transfers (and stores) are in flight
+// (vmcnt: bits 3:0 and 15:14 of the s_waitcnt immediate; they complete in order).
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
-template <int PER>
-__device__ __forceinline__ void wait_stages(int later) {
-  static_assert((kRing - 2) * PER < 64, "the transfers in flight fit the vmcnt counter");
-  if (later >= 3)
-    wait_vmcnt<(kRing >= 5 ? 3 * PER : 0)>();
-  else if (later == 2)
-    wait_vmcnt<2 * PER>();
-  else if (later == 1)
-    wait_vmcnt<PER>();
-  else
-    wait_vmcnt<0>();
-}
 
-// Workgroup barrier without a memory fence (the fence of __syncthreads would also
-// wait for the transfers still in flight for later stages). The LDS data it
-// guards is written only by the transfers, whose completion each wave waits for
-// explicitly; the empty asm keeps the compiler from moving memory accesses
-// across it.
+// Workgroup barrier without a memory fence (the fence of __syncthreads would wait
+// for every transfer in flight). The LDS data it guards is written only by the
+// transfers, whose completion each wave waits for explicitly before it; the empty
+// asm keeps the compiler from moving memory accesses across it.
 __device__ __forceinline__ void bare_barrier() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
@@ -169,383 +122,445 @@ __device__ __forceinline__ void bare_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// One output tile of BM token rows x 256 columns over stages k_lo .. k_hi - 1.
-// BM = 256 (full tiles) or 64 (the ragged last rows of the tokens, and calls of
-// fewer than 256 tokens). Wave (wn, wm) owns a WN x WM block of it (columns x
-// token rows) as kNT x kMT MFMA tiles of 32 x 32:
-//   four waves:  128 x 128 (full), 128 x 32 (tail)
-//   eight waves: 128 x 64 (full),   64 x 32 (tail)
-// The W part of a stage is always 256 rows, the X part BM rows; the first half
-// of the waves copy the W part, the second half the X part, in equal shares.
-template <int BM, bool kAct>
-__device__ __forceinline__ void tile_body(const GemmArgs& a, char* smem, int m0, int n0, int split, int k_lo,
-                                          int k_hi) {
-  constexpr int WN = (BM == kBM || kWaves == 4) ? 128 : 64;   // columns per wave
-  constexpr int NG = kBN / WN;                                // column groups
-  constexpr int WM = BM / (kWaves / NG);                      // token rows per wave
-  constexpr int kNT = WN / 32, kMT = WM / 32;                 // MFMA tiles per wave
-  static_assert(NG * (BM / WM) == kWaves && WM % 32 == 0, "wave blocks tile the output tile");
-  constexpr int kHalf = kWaves / 2;                  // waves per operand part
-  constexpr int kDmaX = (BM / kHalf) / kRowsPerDma;  // transfers per X wave per stage
-  constexpr int kDmaMax = (kBN / kHalf) / kRowsPerDma;   // a W wave's count (the larger)
-  static_assert(kDmaX >= 1, "every X wave copies whole transfers");
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+// One output tile over stages k_lo .. k_hi - 1 of reduction split `split`.
+struct Item {
+  int m0, n0, split, k_lo, k_hi;
+};
 
-  // Transfers: wave w copies its share of one part of every stage: W rows (the
-  // first half of the waves) or X rows (the second half). One transfer covers
-  // kRowsPerDma whole rows (the row's 16-byte chunks spread over kCPR consecutive
-  // lanes); lane L lands at 16 L, i.e. at row position L % kCPR of its row, and
-  // fetches the chunk stored there under the swizzle.
-  const bool is_x = w >= kHalf;
-  const int half = w % kHalf;
-  const int rows_half = is_x ? BM / kHalf : kBN / kHalf;
-  const uint16_t* gptr[kDmaMax];
-  {
-    const uint16_t* base = is_x ? a.x : a.w;
-    const int r0 = (is_x ? m0 : n0) + rows_half * half;
-    const int rmax = (is_x ? a.T : a.N2) - 1;
-#pragma unroll
-    for (int i = 0; i < kDmaMax; ++i) {
-      const int R = rows_half * half + i * kRowsPerDma + lane / kCPR;   // row within the part
-      const int c = (lane % kCPR) ^ swizzle(R);
-      int r = min(r0 + i * kRowsPerDma + lane / kCPR, rmax);           // rows past the edge read the last row
-      if (kAct && !is_x) {
-        // with the gated activation the tile covers features n0 / 2 .. + 127: the
-        // rows of wave column group R / WN are gate rows of WN / 2 features, then
-        // the up rows of the same features (features past the end read the last)
-        const int rr = R % WN;
-        const int f = min(n0 / 2 + (WN / 2) * (R / WN) + rr % (WN / 2), a.I - 1);
-        r = rr < WN / 2 ? f : a.I + f;
-      }
-      gptr[i] = base + size_t(r) * a.H + 8 * c;
-    }
+// Position u of a list of tiles x splits -> tile. The first 8 * (n / 8) positions
+// give XCD u % 8 the contiguous range xcd * (n / 8) + u / 8 (workgroup b runs on
+// XCD b % 8, and the grid is a multiple of 8 whenever it is smaller than the list);
+// the remainder runs in order. Entry v is tile v % tiles of split v / tiles.
+__device__ __forceinline__ Item item_at(const GemmArgs& a, int u, int tiles_m, int bm, int m_first) {
+  Item r;
+  const int ntiles = tiles_m * a.tiles_n;
+  const int per_xcd = ntiles * a.splits / 8;
+  const int v = (u < 8 * per_xcd) ? (u % 8) * per_xcd + u / 8 : u;
+  const int t = v % ntiles;
+  r.split = v / ntiles;
+  const int nk = a.H / kBK, kq = nk / a.splits, kr = nk - kq * a.splits;
+  r.k_lo = r.split * kq + min(r.split, kr);
+  r.k_hi = r.k_lo + kq + (r.split < kr);
+  const int first_m = t / (kGroupM * a.tiles_n) * kGroupM;
+  const int gm = min(kGroupM, tiles_m - first_m);
+  const int in_grp = t - first_m * a.tiles_n;
+  r.m0 = m_first + (first_m + in_grp % gm) * bm;
+  r.n0 = (in_grp / gm) * kBN;
+  return r;
+}
+
+// The main tiles of workgroup b: positions b, b + grid, ...
+struct MainList {
+  int at, n;
+  __device__ __forceinline__ MainList(const GemmArgs& a) {
+    n = a.main_m * a.tiles_n * a.splits;
+    at = blockIdx.x;
   }
-  const int dst0 = (is_x ? kPart : 0) + rows_half * half * kRowBytes;
-  // this wave's transfers i0 .. i0 + n - 1 of stage s (n a compile-time count)
-  auto issue = [&](int s, int i0, auto n) {
-    char* stage = smem + (s % kRing) * kStage + dst0;
-#pragma unroll
-    for (int i = 0; i < decltype(n)::value; ++i)
-      dma16(gptr[i0 + i] + s * kBK, stage + (i0 + i) * kRowsPerDma * kRowBytes);
-  };
-  auto issue_all = [&](int s) {
-    if (is_x)
-      issue(s, 0, std::integral_constant<int, kDmaX>{});
-    else
-      issue(s, 0, std::integral_constant<int, kDmaMax>{});
-  };
-  // transfer i of this wave for stage sd into ring slot `slot` (in tail tiles
-  // the X waves have fewer transfers than the W waves)
-  auto dma_one = [&](int sd, int slot, int i) {
-    if (kDmaX == kDmaMax || !is_x || i < kDmaX)
-      dma16(gptr[i] + sd * kBK, smem + slot * kStage + dst0 + i * kRowsPerDma * kRowBytes);
-  };
-  constexpr int kDmaStep = kDmaMax / kSpread;   // transfers per k-step in the first kSpread k-steps
-  static_assert(kDmaMax % kSpread == 0 && (kDmaX % kDmaStep == 0 || kDmaX < kDmaStep),
-                "transfers split evenly over the k-steps");
+  __device__ __forceinline__ bool more() const { return at < n; }
+  __device__ __forceinline__ void next() { at += gridDim.x; }
+};
 
-  const int wn = w % NG, wm = w / NG;
-  f32x16 acc[kNT][kMT];
-#pragma unroll
-  for (int i = 0; i < kNT; ++i)
-#pragma unroll
-    for (int j = 0; j < kMT; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // Operand fragment (row tile q, k-step j) of lane L: row 32 q + L % 32 of the
-  // wave's rows, chunk 2 j + L / 32; the swizzle term depends on the lane only.
-  int roff[kKSteps];
-#pragma unroll
-  for (int j = 0; j < kKSteps; ++j)
-    roff[j] = (lane & 31) * kRowBytes + 16 * ((2 * j + (lane >> 5)) ^ swizzle(lane & 31));
-
-#pragma unroll
-  for (int s = 0; s < kRing - 1; ++s)
-    if (k_lo + s < k_hi) issue_all(k_lo + s);
-
-  // Entering stage s: this wave's transfers of stage s are done once at most
-  // those of the stages after it are still in flight; the barrier then makes
-  // every wave's part visible and tells that stage s - 1, whose ring slot the
-  // next transfers overwrite, has been read by all waves.
-  auto enter = [&](int s) {
-    const int later = min(k_hi - 1 - s, kRing - 2);
-    if (is_x)
-      wait_stages<kDmaX>(later);
-    else
-      wait_stages<kDmaMax>(later);
-    bare_barrier();
-  };
-  // Operand fragments, double-buffered over k-steps. A k-step's eight reads go
-  // out in two groups, (W 0, W 1, X 0 .. kMT-1) and (W 2, W 3), the first ahead
-  // of the previous k-step's MFMAs and the second halfway through them, so that
-  // at most 14 reads are outstanding (the LDS wait counter holds 15; with more
-  // in flight every wait would have to drain them all).
-  bf16x8 fa[2][kNT], fb[2][kMT];
-  auto stage_ptrs = [&](int s, const char*& wf, const char*& xf) {
-    const char* cur = smem + (s % kRing) * kStage;
-    wf = cur + WN * wn * kRowBytes;
-    xf = cur + kPart + WM * wm * kRowBytes;
-  };
-  auto read_a = [&](int s, int j, int f) {
-    const char *wf, *xf;
-    stage_ptrs(s, wf, xf);
-#pragma unroll
-    for (int q = 0; q < kNT / 2; ++q) fa[f][q] = as_bf16x8(lds16(wf + 32 * q * kRowBytes + roff[j]));
-#pragma unroll
-    for (int q = 0; q < kMT; ++q) fb[f][q] = as_bf16x8(lds16(xf + 32 * q * kRowBytes + roff[j]));
-  };
-  auto read_b = [&](int s, int j, int f) {
-    const char *wf, *xf;
-    stage_ptrs(s, wf, xf);
-#pragma unroll
-    for (int q = kNT / 2; q < kNT; ++q) fa[f][q] = as_bf16x8(lds16(wf + 32 * q * kRowBytes + roff[j]));
-  };
-  constexpr int kN = kNT * kMT;   // MFMAs per k-step: W row tile idx / kMT, X row tile idx % kMT
-  static_assert(kKSteps % 2 == 0, "k-steps alternate the two fragment buffers");
-
-  if (k_lo < k_hi) {
-    enter(k_lo);
-    read_a(k_lo, 0, 0);
-    read_b(k_lo, 0, 0);
+// The small tiles of workgroup b. When the main tiles do not divide evenly, the
+// last grid - rem workgroups have one main tile fewer; each of these takes
+// `light` small tiles first (about the time of a main tile), and the rest are
+// dealt to all workgroups in turn.
+struct SmallList {
+  int at, n, in_light, nlight;
+  __device__ __forceinline__ SmallList(const GemmArgs& a) {
+    const int grid = gridDim.x, b = blockIdx.x;
+    n = a.tail_m * a.tiles_n * a.splits;
+    const int rem = (a.main_m * a.tiles_n * a.splits) % grid;
+    nlight = grid - rem;
+    in_light = min(int64_t(n), int64_t(a.light) * nlight);
+    at = b - rem;
+    if (at < 0 || at >= in_light) at = in_light + b;
   }
-  for (int s = k_lo; s < k_hi; ++s) {
-    // The transfers of stage s + kRing - 1 go into the slot of stage s - 1, which
-    // every wave has finished reading (the barrier of entering s). Past the last
-    // stage they repeat stage k_hi - 1 into that free slot, which keeps the loop
-    // free of branches around them; the waits count them as stages in flight.
-    const int sd = min(s + kRing - 1, k_hi - 1);
-    const int slot = (s + kRing - 1) % kRing;
-#pragma unroll
-    for (int j = 0; j < kKSteps; ++j) {
-      const int f = j & 1;
-      const bool last = j + 1 == kKSteps;
-      if (!last) read_a(s, j + 1, f ^ 1);
-      // this k-step's share of the next stage's transfers, behind the operand
-      // reads so that the matrix cores start without waiting for them
-      if (j < kSpread) {
-#pragma unroll
-        for (int d = 0; d < kDmaStep; ++d) dma_one(sd, slot, j * kDmaStep + d);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      // the MFMAs, with the second read group halfway
-#pragma unroll
-      for (int idx = 0; idx < kN; ++idx) {
-        const int ti = idx / kMT, tj = idx % kMT;
-        acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[f][ti], fb[f][tj], acc[ti][tj], 0, 0, 0);
-        if (!last && idx == kN / 2 - 1) {
-          __builtin_amdgcn_sched_barrier(0);
-          read_b(s, j + 1, f ^ 1);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      if (last) {
-        if (s + 1 < k_hi) {
-          enter(s + 1);
-          read_a(s + 1, 0, 0);
-          read_b(s + 1, 0, 0);
-        }
-        // (outside the condition: a scheduling barrier inside it made the
-        // register allocator spill)
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  }
-  wait_vmem();   // the repeated transfers of the last stages have landed
-  __syncthreads();   // every wave is done with the ring before it holds the output
-
-  // Result register r of MFMA tile (ti, tj): token row 32 tj + L % 32 of the
-  // wave's rows, column 32 ti + 8(r / 4) + 4(L / 32) + r % 4 of its columns.
-  const int mw = m0 + WM * wm, nw = n0 + WN * wn;
-  if (a.splits > 1) {
-    // fp32 partial sums of this split, straight from the accumulators: four
-    // consecutive columns of one token row per (ti, tj, g)
-    float* pb = a.part + size_t(split) * a.T * a.N2;
-#pragma unroll
-    for (int ti = 0; ti < kNT; ++ti)
-#pragma unroll
-      for (int tj = 0; tj < kMT; ++tj) {
-        const int m = mw + 32 * tj + (lane & 31);
-        if (m >= a.T) continue;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          // columns n .. n + 3, valid below `lim`
-          int n = nw + 32 * ti + 8 * g + 4 * (lane >> 5);
-          int lim = a.N2;
-          bool vec = (a.N2 & 3) == 0;
-          if (kAct) {
-            // partials keep the weight-row order: gate feature f at column f,
-            // its up row at I + f (features from I on belong to neither)
-            const int f = n0 / 2 + (WN / 2) * wn + 32 * (ti % (kNT / 2)) + 8 * g + 4 * (lane >> 5);
-            if (f >= a.I) continue;
-            n = ti < kNT / 2 ? f : a.I + f;
-            lim = ti < kNT / 2 ? a.I : a.N2;
-            vec = (a.I & 3) == 0;
-          }
-          float* dst = pb + size_t(m) * a.N2 + n;
-          if (n + 4 <= lim && vec) {
-            *reinterpret_cast<f32x4*>(dst) =
-                f32x4{acc[ti][tj][4 * g], acc[ti][tj][4 * g + 1], acc[ti][tj][4 * g + 2], acc[ti][tj][4 * g + 3]};
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (n + e < lim) dst[e] = acc[ti][tj][4 * g + e];
-          }
-        }
-      }
-    return;
-  }
-
-  if constexpr (kAct) {
-    // silu(gate) * up: MFMA tiles ti and ti + kNT / 2 hold the gate and the up
-    // value of the same (token row, feature) in the same register; the wave's
-    // WN / 2 features x WM rows go to LDS, then out in WN-byte row runs.
-    char* eb = smem + w * kEpiWave;
-#pragma unroll
-    for (int ti = 0; ti < kNT / 2; ++ti)
-#pragma unroll
-      for (int tj = 0; tj < kMT; ++tj)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int row = 32 * tj + (lane & 31);
-          const int col = 32 * ti + 8 * g + 4 * (lane >> 5);
-          float z[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) z[e] = silu_f32(acc[ti][tj][4 * g + e]) * acc[ti + kNT / 2][tj][4 * g + e];
-          u32x2 v;
-          v[0] = pack_bf16x2(z[0], z[1]);
-          v[1] = pack_bf16x2(z[2], z[3]);
-          *reinterpret_cast<u32x2*>(eb + row * kPitch + col * 2) = v;
-        }
-    __syncthreads();
-    constexpr int WF = WN / 2;                       // features per wave
-    constexpr int kLPR = WF / 8, kRPI = 64 / kLPR, kIters = WM / kRPI;
-    const int fw = n0 / 2 + WF * wn;
-    const int fb = fw + 8 * (lane % kLPR);
-    if (mw + WM <= a.T && fw + WF <= a.I) {
-      constexpr int kB = kIters < 8 ? kIters : 8;
-#pragma unroll
-      for (int s0 = 0; s0 < kIters; s0 += kB) {
-        u32x4 v[kB];
-#pragma unroll
-        for (int i = 0; i < kB; ++i)
-          v[i] = lds16(eb + (kRPI * (s0 + i) + lane / kLPR) * kPitch + 16 * (lane % kLPR));
-#pragma unroll
-        for (int i = 0; i < kB; ++i)
-          *reinterpret_cast<u32x4*>(a.y + size_t(mw + kRPI * (s0 + i) + lane / kLPR) * a.I + fb) = v[i];
-      }
-      return;
-    }
-#pragma unroll 4
-    for (int s = 0; s < kIters; ++s) {
-      const int row = kRPI * s + lane / kLPR;
-      const int m = mw + row;
-      if (m >= a.T) break;
-      const u32x4 v = lds16(eb + row * kPitch + 16 * (lane % kLPR));
-      uint16_t* dst = a.y + size_t(m) * a.I + fb;
-      if (fb + 8 <= a.I) {
-        *reinterpret_cast<u32x4*>(dst) = v;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (fb + e < a.I) dst[e] = uint16_t(v[e >> 1] >> (16 * (e & 1)));
-      }
-    }
-    return;
-  }
-
-  // bf16: the wave's block to LDS (token-row major), then out in WN * 2-byte row
-  // runs (kLPR lanes per row, kRPI rows per store instruction).
-  char* eb = smem + w * kEpiWave;
-#pragma unroll
-  for (int ti = 0; ti < kNT; ++ti)
-#pragma unroll
-    for (int tj = 0; tj < kMT; ++tj)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int row = 32 * tj + (lane & 31);
-        const int col = 32 * ti + 8 * g + 4 * (lane >> 5);
-        u32x2 v;
-        v[0] = pack_bf16x2(acc[ti][tj][4 * g], acc[ti][tj][4 * g + 1]);
-        v[1] = pack_bf16x2(acc[ti][tj][4 * g + 2], acc[ti][tj][4 * g + 3]);
-        *reinterpret_cast<u32x2*>(eb + row * kPitch + col * 2) = v;
-      }
-  __syncthreads();
-  constexpr int kLPR = WN / 8, kRPI = 64 / kLPR, kIters = WM / kRPI;
-  const int nb = nw + 8 * (lane % kLPR);
-  if (mw + WM <= a.T && nw + WN <= a.N2) {
-    // interior block: up to eight LDS reads in flight, then their stores
-    constexpr int kB = kIters < 8 ? kIters : 8;
-#pragma unroll
-    for (int s0 = 0; s0 < kIters; s0 += kB) {
-      u32x4 v[kB];
-#pragma unroll
-      for (int i = 0; i < kB; ++i)
-        v[i] = lds16(eb + (kRPI * (s0 + i) + lane / kLPR) * kPitch + 16 * (lane % kLPR));
-#pragma unroll
-      for (int i = 0; i < kB; ++i)
-        *reinterpret_cast<u32x4*>(a.y + size_t(mw + kRPI * (s0 + i) + lane / kLPR) * a.N2 + nb) = v[i];
-    }
-    return;
-  }
-#pragma unroll 4
-  for (int s = 0; s < kIters; ++s) {
-    const int row = kRPI * s + lane / kLPR;
-    const int m = mw + row;
-    if (m >= a.T) break;
-    const u32x4 v = lds16(eb + row * kPitch + 16 * (lane % kLPR));
-    uint16_t* dst = a.y + size_t(m) * a.N2 + nb;
-    if (nb + 8 <= a.N2) {
-      *reinterpret_cast<u32x4*>(dst) = v;
+  __device__ __forceinline__ bool more() const { return at < n; }
+  __device__ __forceinline__ void next() {
+    if (at < in_light) {
+      at += nlight;
+      if (at >= in_light) at = in_light + blockIdx.x;
     } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (nb + e < a.N2) dst[e] = uint16_t(v[e >> 1] >> (16 * (e & 1)));
+      at += gridDim.x;
     }
+  }
+};
+
+// Buffer descriptor of up to `rows` rows of a row-major matrix from row r0 on
+// (rows past the matrix are out of range: they read as zero), in scalar registers.
+struct Rows {
+  uint32_t lo, hi, bytes;
+  __device__ __forceinline__ void set(const uint16_t* p, int r0, int rows_total, int rows, int H) {
+    const int valid = max(0, min(rows, rows_total - r0));
+    const uint64_t b = reinterpret_cast<uint64_t>(p + size_t(valid > 0 ? r0 : 0) * H);
+    lo = uniform(uint32_t(b));
+    hi = uniform(uint32_t(b >> 32));
+    bytes = uniform(uint32_t(valid) * uint32_t(H) * 2);
+  }
+};
+
+#ifdef __HIP_DEVICE_COMPILE__
+// 16 bytes per lane from the rows into LDS: lane L lands at lds + 16 L.
+__device__ __forceinline__ void transfer(const Rows& r, char* lds, uint32_t lane_off, uint32_t stage_off) {
+  const uint64_t b = uint64_t(uniform(r.lo)) | (uint64_t(uniform(r.hi)) << 32);
+  __amdgpu_buffer_rsrc_t d =
+      __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(b), 0, int(uniform(r.bytes)), 0x00020000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(d, (lds_void*)lds, 16, lane_off, uniform(stage_off), 0, 0);
+}
+#endif
+
+// A tile of BM token rows x 256 columns as the waves see it. The W rows of a stage
+// are two units (with the activation: the gate rows and the up rows of 128
+// features); with BM = 256 the X rows are two units as well (four phases per
+// stage, one per pair of units, and a ring of two stages), below that one (two
+// phases, three stages). Wave (wn, wm) owns, of every unit pair, QN columns x QM
+// token rows as kNT x kMT MFMA tiles.
+template <int BM>
+struct Tile {
+  static constexpr int XH = BM == 256 ? 2 : 1;             // X units
+  static constexpr int WNW = BM == 256 ? 2 : 4;            // waves along the columns
+  static constexpr int HM = BM / XH;                       // rows of an X unit
+  static constexpr int QN = kHN / WNW, QM = HM / (kWaves / WNW);
+  static constexpr int kNT = QN / 16, kMT = QM / 16;
+  static constexpr int kRing = BM == 256 ? 2 : 3;
+  static constexpr int kStage = (kBN + BM) * kRow;
+  static constexpr int kOffX = kBN * kRow;
+  static constexpr int kDW = kHN / 8 / kWaves, kDX = HM / 8 / kWaves;   // transfers per wave and unit
+  static constexpr int kEpiRows = QN == 64 ? QM : 32;      // rows staged at a time in the epilogue
+  static constexpr int kEpi = QN * kEpiRows * 2;           // a wave's staging bytes
+  static_assert(kRing * kStage + kWaves * kEpi <= kSmem, "the ring and the staging areas fit");
+  static_assert(kDW * 8 * kWaves == kHN && kDX * 8 * kWaves == HM && kDX >= 1, "whole transfers per wave");
+  static_assert(QM % kEpiRows == 0 && kEpiRows % 16 == 0, "whole staged blocks");
+};
+
+// fp32 partial sums of one 16 x 16 result: columns n .. n + 3 of token row m,
+// valid below `lim`, n and lim relative to the row.
+__device__ __forceinline__ void store_part(float* row, int n, int lim, bool vec, f32x4 v) {
+  if (n + 4 <= lim && vec) {
+    *reinterpret_cast<f32x4*>(row + n) = v;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (n + e < lim) row[n + e] = v[e];
   }
 }
 
-template <bool kAct>
-__global__ __launch_bounds__(kThreads, 1) void gateup_kernel(GemmArgs a) {
-  __shared__ __attribute__((aligned(1024))) char smem[kSmem];
-
-  // Work item q -> (tile, split): the first 8 * (items / 8) items give XCD q % 8
-  // the contiguous range xcd * (items / 8) + q / 8 (workgroup b runs on XCD b % 8,
-  // and the grid is a multiple of 8 whenever it is smaller than the item count);
-  // the remainder runs in order. Item u is tile u % tiles of reduction split
-  // u / tiles, so the workgroups next to each other on an XCD work on
-  // neighbouring tiles of the same split. Tiles 0 .. full - 1 are the 256-row
-  // tiles (in groups of 8 that share a weight tile), the rest the 64-row tiles of
-  // the last T % 256 rows. A workgroup takes items blockIdx.x, + gridDim.x, ...
-  const int full = a.tiles_m * a.tiles_n;
-  const int ntiles = full + a.tail_m * a.tiles_n;
-  const int nitems = ntiles * a.splits;
-  const int per_xcd = nitems / 8;
-  const int nk_all = a.H / kBK;
-  for (int q = blockIdx.x; q < nitems; q += gridDim.x) {
-    const int u = (q < 8 * per_xcd) ? (q % 8) * per_xcd + q / 8 : q;
-    const int t = u % ntiles;
-    const int split = u / ntiles;
-    const int k_lo = int(int64_t(split) * nk_all / a.splits);
-    const int k_hi = int(int64_t(split + 1) * nk_all / a.splits);
-    if (t < full) {
-      const int grp = t / (kGroupM * a.tiles_n);
-      const int first_m = grp * kGroupM;
-      const int gm = min(kGroupM, a.tiles_m - first_m);
-      const int in_grp = t - grp * kGroupM * a.tiles_n;
-      tile_body<kBM, kAct>(a, smem, (first_m + in_grp % gm) * kBM, (in_grp / gm) * kBN, split, k_lo, k_hi);
-    } else {
-      const int tt = t - full;
-      tile_body<kBMTail, kAct>(a, smem, a.tiles_m * kBM + (tt % a.tail_m) * kBMTail, (tt / a.tail_m) * kBN,
-                               split, k_lo, k_hi);
+// A wave's kEpiRows x QN block of bf16 results, staged in LDS by `put` in an
+// XOR-swizzled order, to rows m.. and columns n.. of y (T rows, `cols` columns).
+template <int QN, int ROWS>
+struct Staged {
+  static constexpr int kLPR = QN / 8, kRPI = 64 / kLPR, kIt = ROWS / kRPI;
+  static constexpr int kShift = kLPR == 8 ? 1 : 2;   // rows that share a 256-byte bank run
+  __device__ static __forceinline__ void put(char* eb, int row, int col, float v0, float v1, float v2, float v3) {
+    u32x2 v;
+    v[0] = pack_bf16x2(v0, v1);
+    v[1] = pack_bf16x2(v2, v3);
+    *reinterpret_cast<u32x2*>(eb + row * QN * 2 + 16 * ((col >> 3) ^ ((row >> kShift) & (kLPR - 1))) +
+                              2 * (col & 7)) = v;
+  }
+  __device__ static __forceinline__ void out(const char* eb, int lane, uint16_t* y, int m, int n, int T, int cols) {
+    u32x4 v[kIt];
+#pragma unroll
+    for (int i = 0; i < kIt; ++i) v[i] = lds16(eb + 1024 * i + 16 * lane);
+#pragma unroll
+    for (int i = 0; i < kIt; ++i) {
+      const int row = i * kRPI + lane / kLPR;
+      const int c = n + 8 * ((lane % kLPR) ^ ((row >> kShift) & (kLPR - 1)));
+      if (m + row >= T) continue;
+      uint16_t* dst = y + size_t(m + row) * cols + c;
+      if (c + 8 <= cols) {
+        *reinterpret_cast<u32x4*>(dst) = v[i];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (c + e < cols) dst[e] = uint16_t(v[i][e >> 1] >> (16 * (e & 1)));
+      }
     }
-    // the next item's transfers overwrite the LDS this item's epilogue has read;
-    // its stores may still be in flight
-    __builtin_amdgcn_s_waitcnt(0xC07F);
+  }
+};
+
+// Every tile of this workgroup's list, in turn.
+template <int BM, bool kAct, typename List>
+__device__ __forceinline__ void run_tiles(const GemmArgs& a, char* smem, int m_first, int tiles_m) {
+#ifdef __HIP_DEVICE_COMPILE__
+  using C = Tile<BM>;
+  constexpr int QN = C::QN, QM = C::QM, kNT = C::kNT, kMT = C::kMT;
+  List todo(a);
+  if (!todo.more()) return;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool late = w >= kWaves / 2;   // the half that runs half a phase behind
+  const int wn = w % C::WNW, wm = w / C::WNW;
+
+  // Transfers. One covers eight rows of a unit: lane L lands at row L / 8, position
+  // L % 8, and fetches the chunk stored there under the swizzle (row R keeps chunk
+  // c at c ^ (R / 2) % 8). Stage `dk` of the list's tile `ahead` goes to ring slot
+  // `dslot`.
+  uint32_t vw[C::kDW], vx[C::kDX];
+  {
+    auto lane_off = [&](int r) {
+      return uint32_t(r) * (uint32_t(a.H) * 2) + 16 * ((lane & 7) ^ ((r >> 1) & 7));
+    };
+#pragma unroll
+    for (int i = 0; i < C::kDW; ++i) vw[i] = lane_off((w * C::kDW + i) * 8 + lane / 8);
+#pragma unroll
+    for (int i = 0; i < C::kDX; ++i) vx[i] = lane_off((w * C::kDX + i) * 8 + lane / 8);
+  }
+  Rows rw[2], rx[C::XH];
+  List ahead(a);
+  int dk, dk_hi, dslot = 0;
+  auto aim = [&]() {
+    const Item it = item_at(a, ahead.at, tiles_m, BM, m_first);
+    if (kAct) {
+      rw[0].set(a.w, it.n0 / 2, a.I, kHN, a.H);
+      rw[1].set(a.w + size_t(a.I) * a.H, it.n0 / 2, a.I, kHN, a.H);
+    } else {
+      rw[0].set(a.w, it.n0, a.N2, kHN, a.H);
+      rw[1].set(a.w, it.n0 + kHN, a.N2, kHN, a.H);
+    }
+#pragma unroll
+    for (int g = 0; g < C::XH; ++g) rx[g].set(a.x, it.m0 + g * C::HM, a.T, C::HM, a.H);
+    dk = it.k_lo;
+    dk_hi = it.k_hi;
+  };
+  aim();
+  auto issue_w = [&](int h) {
+#pragma unroll
+    for (int i = 0; i < C::kDW; ++i)
+      transfer(rw[h], smem + dslot * C::kStage + h * kHN * kRow + (w * C::kDW + i) * 1024, vw[i], dk * kRow);
+  };
+  auto issue_x = [&](int g) {
+#pragma unroll
+    for (int i = 0; i < C::kDX; ++i)
+      transfer(rx[g], smem + dslot * C::kStage + C::kOffX + g * C::HM * kRow + (w * C::kDX + i) * 1024, vx[i],
+               dk * kRow);
+  };
+  auto next_stage = [&]() {
+    dslot = dslot + 1 == C::kRing ? 0 : dslot + 1;
+    if (++dk == dk_hi) {
+      List n = ahead;
+      n.next();
+      if (n.more()) {
+        ahead = n;
+        aim();
+      } else {
+        // past the last tile: its last stage again, into slots that nobody reads
+        // (the waits count transfers, so their number stays the same)
+        --dk;
+      }
+    }
+  };
+
+  // Operand fragments: (row tile t, 32-feature step j) of lane L is row 16 t + L % 16,
+  // chunk 4 j + L / 16; the swizzle term depends on the lane only.
+  int aw[2], ax[2], rslot = 0;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int r = lane & 15;
+    const int o = r * kRow + 16 * ((4 * j + (lane >> 4)) ^ ((r >> 1) & 7));
+    aw[j] = wn * QN * kRow + o;
+    ax[j] = C::kOffX + wm * QM * kRow + o;
+  }
+  bf16x8 fw[2][kNT][2], fx[C::XH][kMT][2];
+  f32x4 acc[2][C::XH][kNT][kMT];
+  auto read_w = [&](int h) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int t = 0; t < kNT; ++t) fw[h][t][j] = as_bf16x8(lds16(smem + aw[j] + (h * kHN + 16 * t) * kRow));
+  };
+  auto read_x = [&](int g) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int t = 0; t < kMT; ++t) fx[g][t][j] = as_bf16x8(lds16(smem + ax[j] + (g * C::HM + 16 * t) * kRow));
+  };
+  auto next_slot = [&]() {
+    const int step = rslot + 1 == C::kRing ? -(C::kRing - 1) * C::kStage : C::kStage;
+    rslot = rslot + 1 == C::kRing ? 0 : rslot + 1;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      aw[j] += step;
+      ax[j] += step;
+    }
+  };
+  // The MFMAs of one phase; the first stage of a tile starts the sums from zero.
+  auto mma = [&](int h, int g, bool first) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int tj = 0; tj < kMT; ++tj)
+#pragma unroll
+        for (int ti = 0; ti < kNT; ++ti) {
+          const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+          acc[h][g][ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              fw[h][ti][j], fx[g][tj][j], (first && j == 0) ? zero : acc[h][g][ti][tj], 0, 0, 0);
+        }
+  };
+
+  // One stage. BM = 256, phases (W unit, X unit): (0,0) (0,1) (1,1) (1,0). The
+  // memory slots read X 0; X 1; W 1; W 0 of the next stage, and issue W 1 of the
+  // stage after next; then W 0, X 0, X 1 of the one after that: each unit two
+  // phases after its buffer was last read, and five units behind the one the next
+  // phase needs. BM < 256, phases W 0 and W 1: the slots read X and W 0; W 1, and
+  // issue X and W 0, then W 1, two stages ahead of the reads.
+  auto stage = [&](bool first) {
+    if constexpr (BM == 256) {
+      constexpr int kWaitA = 3 * C::kDX + 2 * C::kDW, kWaitB = 2 * C::kDX + 3 * C::kDW;
+      issue_w(1);
+      __builtin_amdgcn_sched_barrier(0);
+      read_x(0);
+      wait_vmcnt<kWaitB>();
+      bare_barrier();
+      mma(0, 0, first);
+      bare_barrier();
+      next_stage();
+      issue_w(0);
+      __builtin_amdgcn_sched_barrier(0);
+      read_x(1);
+      wait_vmcnt<kWaitB>();
+      bare_barrier();
+      mma(0, 1, first);
+      bare_barrier();
+      issue_x(0);
+      __builtin_amdgcn_sched_barrier(0);
+      read_w(1);
+      wait_vmcnt<kWaitA>();
+      bare_barrier();
+      mma(1, 1, first);
+      bare_barrier();
+      issue_x(1);
+      __builtin_amdgcn_sched_barrier(0);
+      next_slot();
+      read_w(0);
+      wait_vmcnt<kWaitA>();
+      bare_barrier();
+      mma(1, 0, first);
+    } else {
+      issue_x(0);
+      issue_w(0);
+      __builtin_amdgcn_sched_barrier(0);
+      read_x(0);
+      read_w(0);
+      wait_vmcnt<2 * (C::kDX + C::kDW) + C::kDW>();
+      bare_barrier();
+      mma(0, 0, first);
+      bare_barrier();
+      issue_w(1);
+      __builtin_amdgcn_sched_barrier(0);
+      read_w(1);
+      next_slot();
+      wait_vmcnt<C::kDX + 3 * C::kDW>();
+      bare_barrier();
+      mma(1, 0, first);
+      next_stage();
+    }
+  };
+
+  if constexpr (BM == 256) {
+    issue_w(0);
+    issue_x(0);
+    issue_x(1);
+    issue_w(1);
+    next_stage();
+    issue_w(0);
+    issue_x(0);
+    issue_x(1);
+    wait_vmcnt<3 * C::kDX + 2 * C::kDW>();   // W 0 and X 0 of the first stage have landed
+    bare_barrier();
+    read_w(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);      // W 0 is read before its buffer may be refilled
+    bare_barrier();
+  } else {
+    for (int s = 0; s < 2; ++s) {
+      issue_x(0);
+      issue_w(0);
+      issue_w(1);
+      next_stage();
+    }
+    wait_vmcnt<C::kDX + 3 * C::kDW>();       // X and W 0 of the first stage have landed
     bare_barrier();
   }
+  if (late) bare_barrier();
+
+  for (; todo.more(); todo.next()) {
+    const Item it = item_at(a, todo.at, tiles_m, BM, m_first);
+    stage(true);
+    for (int k = it.k_lo + 1; k < it.k_hi; ++k) {
+      bare_barrier();
+      stage(false);
+    }
+    // Results, in the MFMA slot of the last phase: element r of acc[h][g][ti][tj] is
+    // token row 16 tj + L % 16 of the wave's rows of X unit g, column 16 ti + 4 (L / 16)
+    // + r of its columns of W unit h.
+    if (a.splits > 1) {
+      float* pb = a.part + size_t(it.split) * a.T * a.N2;
+#pragma unroll
+      for (int g = 0; g < C::XH; ++g)
+#pragma unroll
+        for (int tj = 0; tj < kMT; ++tj) {
+          const int m = it.m0 + g * C::HM + wm * QM + 16 * tj + (lane & 15);
+          if (m >= a.T) continue;
+          float* row = pb + size_t(m) * a.N2;
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int ti = 0; ti < kNT; ++ti) {
+              const int c = wn * QN + 16 * ti + 4 * (lane >> 4);
+              if (kAct) {
+                // partials keep the weight-row order: gate feature f at column f, its up
+                // row at I + f (features from I on belong to neither)
+                const int f = it.n0 / 2 + c;
+                if (f < a.I) store_part(row + h * a.I, f, a.I, (a.I & 3) == 0, acc[h][g][ti][tj]);
+              } else {
+                store_part(row, it.n0 + h * kHN + c, a.N2, (a.N2 & 3) == 0, acc[h][g][ti][tj]);
+              }
+            }
+        }
+    } else {
+      char* eb = smem + C::kRing * C::kStage + w * C::kEpi;
+      using S = Staged<QN, C::kEpiRows>;
+      constexpr int kTB = C::kEpiRows / 16;   // row tiles staged at a time
+      const int ncols = kAct ? a.I : a.N2;
+#pragma unroll
+      for (int h = 0; h < (kAct ? 1 : 2); ++h)
+#pragma unroll
+        for (int g = 0; g < C::XH; ++g)
+#pragma unroll
+          for (int tb = 0; tb < kMT; tb += kTB) {
+#pragma unroll
+            for (int tj = 0; tj < kTB; ++tj)
+#pragma unroll
+              for (int ti = 0; ti < kNT; ++ti) {
+                const f32x4 v = acc[h][g][ti][tb + tj];
+                const int row = 16 * tj + (lane & 15), col = 16 * ti + 4 * (lane >> 4);
+                if constexpr (kAct) {
+                  const f32x4 u = acc[1][g][ti][tb + tj];
+                  S::put(eb, row, col, silu_f32(v[0]) * u[0], silu_f32(v[1]) * u[1], silu_f32(v[2]) * u[2],
+                         silu_f32(v[3]) * u[3]);
+                } else {
+                  S::put(eb, row, col, v[0], v[1], v[2], v[3]);
+                }
+              }
+            S::out(eb, lane, a.y, it.m0 + g * C::HM + wm * QM + 16 * tb,
+                   (kAct ? it.n0 / 2 : it.n0 + h * kHN) + wn * QN, a.T, ncols);
+          }
+    }
+    bare_barrier();
+  }
+  if (!late) bare_barrier();
+  wait_vmcnt<0>();   // no transfer outlives its buffers
+  bare_barrier();
+#endif
+}
+
+// Main tiles of BM token rows (256 or 128; none when main_m is 0), then the 64-row
+// tiles of the rows after them.
+template <int BM, bool kAct>
+__global__ __launch_bounds__(kThreads, 1) void gateup_kernel(GemmArgs a) {
+  __shared__ __attribute__((aligned(1024))) char smem[kSmem];
+  run_tiles<BM, kAct, MainList>(a, smem, 0, a.main_m);
+  run_tiles<kTailBM, kAct, SmallList>(a, smem, a.main_m * BM, a.tail_m);
 }
 
 // y = bf16(sum over splits of the partials), the splits summed in order; thread i
@@ -608,8 +623,55 @@ __global__ __launch_bounds__(256) void gateup_act_reduce_kernel(const float* par
 
 }  // namespace
 
+namespace {
+
+// How a call is tiled and split.
+struct Shape {
+  int bm = 0;               // main tiles of 256 or 128 rows; 64: small tiles only
+  int splits = 1;
+  int32_t main_m = 0, tail_m = 0, light = 0;
+  int64_t items = 0;
+  double cost = 0;
+};
+
+// Microseconds of one stage and, beside the stages, of one tile, by tile rows; of
+// the reducing launch, and of its partial sums' bytes; and the share by which a
+// full chip slows every stage. Fitted to 520 timed calls (64 to 8,200 tokens, the
+// decoder layer's four projections, every tile shape and split; 8 % rms), over
+// which the choice made with them is 0.8 % slower than the best one on average.
+constexpr double kStage256 = 0.92, kStage128 = 0.66, kStage64 = 0.53;
+constexpr double kTile256 = 5.3, kTile128 = 1.4, kTile64 = 0.4;
+constexpr double kReduce = 4.25, kPartBytes = 5.5e6, kLoaded = 0.186;
+
+Shape shape_cost(int32_t T, int32_t H, int32_t N2, int grid_max, int bm, int splits) {
+  Shape s;
+  s.bm = bm;
+  s.splits = splits;
+  const int64_t tiles_n = (N2 + kBN - 1) / kBN;
+  s.main_m = bm == kTailBM ? 0 : T / bm;
+  const int64_t rest = T - int64_t(s.main_m) * bm;
+  s.tail_m = int32_t((rest + kTailBM - 1) / kTailBM);
+  const int64_t nf = s.main_m * tiles_n * splits, ns = s.tail_m * tiles_n * splits;
+  s.items = nf + ns;
+  const double nk = double(H / kBK) / splits;
+  const double cf = bm == 256 ? nk * kStage256 + kTile256 : nk * kStage128 + kTile128;
+  const double cs = nk * kStage64 + kTile64;
+  s.light = std::max(0, int(cf / cs));
+  const int64_t grid = std::min<int64_t>(s.items, grid_max);
+  const int64_t rem = nf % grid, light = grid - rem;
+  const int64_t in_light = std::min<int64_t>(ns, s.light * light);
+  const int64_t extra = (ns - in_light + grid - 1) / grid;
+  const double t_light = double(nf / grid) * cf + double((in_light + light - 1) / light + extra) * cs;
+  const double t_heavy = rem ? double(nf / grid + 1) * cf + double(extra) * cs : 0;
+  s.cost = std::max(t_light, t_heavy) * (1 + kLoaded * std::min(1.0, double(s.items) / grid_max));
+  if (splits > 1) s.cost += kReduce + 2.0 * splits * double(T) * N2 * 4 / kPartBytes;
+  return s;
+}
+
+}  // namespace
+
 int64_t gateup_tiles(int32_t T, int32_t N2) {
-  return (int64_t(T / kBM) + (T % kBM + kBMTail - 1) / kBMTail) * ((N2 + kBN - 1) / kBN);
+  return (int64_t(T / 256) + (T % 256 + kTailBM - 1) / kTailBM) * ((N2 + kBN - 1) / kBN);
 }
 
 int gateup_splits(int32_t T, int32_t H, int32_t N2, int cus) {
@@ -625,36 +687,62 @@ size_t gateup_workspace_bytes(int32_t T, int32_t N2, int splits) {
 }
 
 hipError_t launch_gateup(const uint16_t* x, const uint16_t* w, uint16_t* y, int32_t T, int32_t H, int32_t N2,
-                         bool act, int splits, float* part, int cus, hipStream_t stream, hipEvent_t ev_start,
+                         bool act, int max_splits, float* part, int cus, hipStream_t stream, hipEvent_t ev_start,
                          hipEvent_t ev_stop) {
-  GemmArgs a;
-  a.x = x;
-  a.w = w;
-  a.y = y;
-  a.part = part;
-  a.T = T;
-  a.H = H;
-  a.N2 = N2;
-  a.tiles_m = T / kBM;
-  a.tail_m = (T % kBM + kBMTail - 1) / kBMTail;
-  a.tiles_n = (N2 + kBN - 1) / kBN;
-  a.splits = splits;
-  a.I = N2 / 2;
-  const int64_t n = gateup_tiles(T, N2) * splits;
-  if (n <= 0) return hipSuccess;
-  if (n > INT32_MAX || splits < 1 || splits > H / kBK || (splits > 1 && !part) || (act && N2 % 2 != 0))
+  if (T <= 0) return hipSuccess;
+  if (max_splits < 1 || max_splits > H / kBK || (max_splits > 1 && !part) || (act && N2 % 2 != 0))
     return hipErrorInvalidValue;
-  // one workgroup per compute unit, each looping over its items (a multiple of 8
-  // workgroups, so that every workgroup stays on one XCD's share of the items)
-  const int64_t slots = kPersist ? std::max(8, cus / 8 * 8) : n;
-  const int64_t grid = std::min<int64_t>(n, slots);
-  if (act)
-    hipExtLaunchKernelGGL(gateup_kernel<true>, dim3(unsigned(grid)), dim3(kThreads), 0, stream, ev_start,
-                          splits > 1 ? nullptr : ev_stop, 0, a);
-  else
-    hipExtLaunchKernelGGL(gateup_kernel<false>, dim3(unsigned(grid)), dim3(kThreads), 0, stream, ev_start,
-                          splits > 1 ? nullptr : ev_stop, 0, a);
-  hipError_t e = hipGetLastError();
+  int splits = max_splits;
+  hipError_t e;
+  // The transfers need 16-byte aligned rows and 32-bit offsets within a unit.
+  const bool regular = reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(w) % 16 == 0 &&
+                       int64_t(H) * 2 < kMaxPitch;
+  if (regular) {
+    // one workgroup per compute unit (a multiple of 8, so that each stays on one XCD's
+    // share of the tiles)
+    const int grid_max = std::max(8, cus / 8 * 8);
+    Shape best;
+    for (int bm : {256, 128, 64})
+      for (int s = 1; s <= max_splits; ++s) {
+        const Shape c = shape_cost(T, H, N2, grid_max, bm, s);
+        if (c.items > INT32_MAX / 2) continue;
+        if (best.bm == 0 || c.cost < best.cost) best = c;
+      }
+    if (best.bm == 0) return hipErrorInvalidValue;
+    splits = best.splits;
+    GemmArgs a;
+    a.x = x;
+    a.w = w;
+    a.y = y;
+    a.part = part;
+    a.T = T;
+    a.H = H;
+    a.N2 = N2;
+    a.I = N2 / 2;
+    // with the activation a tile holds 128 features and their two weight rows each
+    a.tiles_n = (N2 + kBN - 1) / kBN;
+    a.main_m = best.main_m;
+    a.tail_m = best.tail_m;
+    a.splits = splits;
+    a.light = best.light;
+    const dim3 grid(unsigned(std::min<int64_t>(best.items, grid_max)));
+    hipEvent_t ev = splits > 1 ? nullptr : ev_stop;
+    if (best.bm == 256) {
+      if (act)
+        hipExtLaunchKernelGGL((gateup_kernel<256, true>), grid, dim3(kThreads), 0, stream, ev_start, ev, 0, a);
+      else
+        hipExtLaunchKernelGGL((gateup_kernel<256, false>), grid, dim3(kThreads), 0, stream, ev_start, ev, 0, a);
+    } else {
+      if (act)
+        hipExtLaunchKernelGGL((gateup_kernel<128, true>), grid, dim3(kThreads), 0, stream, ev_start, ev, 0, a);
+      else
+        hipExtLaunchKernelGGL((gateup_kernel<128, false>), grid, dim3(kThreads), 0, stream, ev_start, ev, 0, a);
+    }
+    e = hipGetLastError();
+  } else {
+    e = launch_gateup_any(x, w, y, T, H, N2, act, splits, part, cus, stream, ev_start,
+                          splits > 1 ? nullptr : ev_stop);
+  }
   if (e != hipSuccess || splits == 1) return e;
   const int64_t total = act ? int64_t(T) * (N2 / 2) : int64_t(T) * N2;
   const int64_t blocks = (total + 1023) / 1024;

@@ -119,3 +119,39 @@ def test_zero_tokens_is_a_no_op_and_bad_sizes_are_refused(lib):
     with pytest.raises(ppas.PPASError) as ex:
         ppas.gateup_proj(x, w, y)
     assert ex.value.status == ppas.PPAS_EUNSUPPORTED
+
+
+@pytest.mark.parametrize("T,H,N", [
+    # 64-row tiles only: one row over a tile; single-stage tiles, several per workgroup
+    (65, 64, 300), (449, 64, 22016), (1790, 64, 9000),
+    # 128-row tiles, then 64-row tiles of the last rows; three stages; splits
+    (130, 2048, 22010), (513, 192, 22000), (700, 11008, 2048),
+    # 256-row tiles, then 64-row tiles dealt to the workgroups with fewer of them
+    (321, 2048, 22016), (577, 1024, 16000), (2048, 11008, 300)])
+def test_tile_shapes_every_element(lib, T, H, N):
+    """Sizes at which each tile shape is chosen, with ragged rows, columns and stage counts."""
+    print(f"gate-up tiles T={T} H={H} N={N}", flush=True)
+    xb = I.gateup_tokens(6, T, 0, hidden=H)
+    wb = I.gateup_weight(6, hidden=H, inter=(N + 1) // 2)[:N]
+    check(f64(lib, run(lib, xb, wb)), xb, wb, label=f"T{T} H{H} N{N}")
+
+
+@pytest.mark.parametrize("which", ["x", "w"])
+def test_operands_off_the_16_byte_grid(lib, which):
+    """Operands that start 8 bytes off a 16-byte boundary take the general kernel."""
+    ppas, step, torch = lib
+    T, H, N = 300, 256, 520
+    xb = I.gateup_tokens(7, T, 0, hidden=H)
+    wb = I.gateup_weight(7, hidden=H, inter=N // 2)
+
+    def off(bits):
+        flat = torch.zeros(bits.size + 4, dtype=torch.bfloat16, device="cuda")
+        flat[4:] = step.to_device_bf16(bits).flatten()
+        return flat[4:].view(*bits.shape)
+
+    x = off(xb) if which == "x" else step.to_device_bf16(xb)
+    w = off(wb) if which == "w" else step.to_device_bf16(wb)
+    assert (x.data_ptr() | w.data_ptr()) % 16 == 8
+    y = torch.full((T, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ppas.gateup_proj(x, w, y)
+    check(f64(lib, y), xb, wb, label=f"{which} off by 8 bytes")

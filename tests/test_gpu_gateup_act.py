@@ -125,3 +125,13 @@ def test_shapes_and_sizes_are_refused(lib):
     with pytest.raises(ppas.PPASError) as ex:
         ppas.gateup_act(x, w, torch.zeros((4, 4), dtype=torch.bfloat16, device="cuda"))
     assert ex.value.status == ppas.PPAS_EUNSUPPORTED
+
+
+@pytest.mark.parametrize("T,H,NI", [(65, 64, 150), (130, 2048, 11005), (513, 192, 11000), (321, 2048, 11008),
+                                    (577, 1024, 8000), (700, 2048, 1030)])
+def test_tile_shapes_every_element(lib, T, H, NI):
+    """Sizes at which each tile shape is chosen, with ragged rows, features and stage counts."""
+    print(f"gate-up-act tiles T={T} H={H} I={NI}", flush=True)
+    xb = I.gateup_tokens(8, T, 0, hidden=H)
+    wb = I.gateup_weight(8, hidden=H, inter=NI)
+    check(f64(run(lib, xb, wb)), xb, wb, label=f"act T{T} H{H} I{NI}")
