@@ -321,7 +321,7 @@ int32_t ppas_plan_items(const ppas_shape* shape, const ppas_seq* seqs, int32_t n
  * the caller. fp32 accumulation, output rounded to bf16 nearest-even; the
  * activation that follows is not applied. When a call's 256 x 256 output
  * tiles are fewer than the device's compute units, the reduction over hidden
- * is split across several workgroups per tile; their fp32 partial sums go to
+ * may be split across several workgroups per tile; their fp32 partial sums go to
  * the caller's workspace (ppas_gateup_workspace_bytes, device memory, not read
  * before written, not shared with a call still in flight) and a second launch
  * adds them in a fixed order. A workspace smaller than that (NULL with 0 bytes

@@ -45,6 +45,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 
@@ -84,6 +85,7 @@ struct GemmArgs {
   int32_t tail_m;         // 64-row tiles of the rows after them
   int32_t splits;         // reduction split over this many workgroups per tile
   int32_t light;          // small tiles a workgroup with one main tile fewer takes first
+  int32_t block;          // stages per block of a two-level sum (tiles below 256 rows, few-row calls)
 };
 
 __device__ __forceinline__ u32x4 lds16(const char* p) { return *reinterpret_cast<const u32x4*>(p); }
@@ -223,6 +225,7 @@ struct Tile {
   static constexpr int QN = kHN / WNW, QM = HM / (kWaves / WNW);
   static constexpr int kNT = QN / 16, kMT = QM / 16;
   static constexpr int kRing = BM == 256 ? 2 : 3;
+  static constexpr bool kTwoLevel = BM != 256;             // block sums added to a running total
   static constexpr int kStage = (kBN + BM) * kRow;
   static constexpr int kOffX = kBN * kRow;
   static constexpr int kDW = kHN / 8 / kWaves, kDX = HM / 8 / kWaves;   // transfers per wave and unit
@@ -485,12 +488,38 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& a, char* smem, int m_f
 
   for (; todo.more(); todo.next()) {
     const Item it = item_at(a, todo.at, tiles_m, BM, m_first);
-    stage(true);
-    for (int k = it.k_lo + 1; k < it.k_hi; ++k) {
-      bare_barrier();
-      stage(false);
+    // Below 256 rows the sums are kept in two levels, blocks of a.block stages added
+    // to a running total: one chain over 2,048 features rounds 1.6 times as far off as
+    // eight partial sums (blocks of eight stages cost 2-4 % of a tile, of four 3-9 %).
+    f32x4 total[2][C::XH][kNT][kMT];
+    if (C::kTwoLevel) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int ti = 0; ti < kNT; ++ti)
+#pragma unroll
+          for (int tj = 0; tj < kMT; ++tj) total[h][0][ti][tj] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    // Results, in the MFMA slot of the last phase: element r of acc[h][g][ti][tj] is
+    for (int k = it.k_lo; k < it.k_hi;) {
+      const int k_end = C::kTwoLevel ? min(k + a.block, it.k_hi) : it.k_hi;
+      if (k > it.k_lo) bare_barrier();
+      stage(true);
+      for (++k; k < k_end; ++k) {
+        bare_barrier();
+        stage(false);
+      }
+      if (C::kTwoLevel) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int ti = 0; ti < kNT; ++ti)
+#pragma unroll
+            for (int tj = 0; tj < kMT; ++tj)
+              total[h][0][ti][tj] += acc[h][0][ti][tj];
+      }
+    }
+    const auto& sum = C::kTwoLevel ? total : acc;
+    // Results, in the MFMA slot of the last phase: element r of sum[h][g][ti][tj] is
     // token row 16 tj + L % 16 of the wave's rows of X unit g, column 16 ti + 4 (L / 16)
     // + r of its columns of W unit h.
     if (a.splits > 1) {
@@ -511,9 +540,9 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& a, char* smem, int m_f
                 // partials keep the weight-row order: gate feature f at column f, its up
                 // row at I + f (features from I on belong to neither)
                 const int f = it.n0 / 2 + c;
-                if (f < a.I) store_part(row + h * a.I, f, a.I, (a.I & 3) == 0, acc[h][g][ti][tj]);
+                if (f < a.I) store_part(row + h * a.I, f, a.I, (a.I & 3) == 0, sum[h][g][ti][tj]);
               } else {
-                store_part(row, it.n0 + h * kHN + c, a.N2, (a.N2 & 3) == 0, acc[h][g][ti][tj]);
+                store_part(row, it.n0 + h * kHN + c, a.N2, (a.N2 & 3) == 0, sum[h][g][ti][tj]);
               }
             }
         }
@@ -532,10 +561,10 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& a, char* smem, int m_f
             for (int tj = 0; tj < kTB; ++tj)
 #pragma unroll
               for (int ti = 0; ti < kNT; ++ti) {
-                const f32x4 v = acc[h][g][ti][tb + tj];
+                const f32x4 v = sum[h][g][ti][tb + tj];
                 const int row = 16 * tj + (lane & 15), col = 16 * ti + 4 * (lane >> 4);
                 if constexpr (kAct) {
-                  const f32x4 u = acc[1][g][ti][tb + tj];
+                  const f32x4 u = sum[1][g][ti][tb + tj];
                   S::put(eb, row, col, silu_f32(v[0]) * u[0], silu_f32(v[1]) * u[1], silu_f32(v[2]) * u[2],
                          silu_f32(v[3]) * u[3]);
                 } else {
@@ -561,6 +590,202 @@ __global__ __launch_bounds__(kThreads, 1) void gateup_kernel(GemmArgs a) {
   __shared__ __attribute__((aligned(1024))) char smem[kSmem];
   run_tiles<BM, kAct, MainList>(a, smem, 0, a.main_m);
   run_tiles<kTailBM, kAct, SmallList>(a, smem, a.main_m * BM, a.tail_m);
+}
+
+// Few token rows (decode iterations): the weights are streamed once and the rest
+// has to stay out of the way. A workgroup owns G tiles of WR weight rows (with
+// the activation half of them gate rows, half the up rows of the same features)
+// x 16 XT token rows, and its waves split the reduction between them in
+// 64-feature chunks, so that no operand is shared between waves: each runs a ring
+// of its own in LDS, kSlots chunks deep, with no barrier until the end and up to
+// 160 KB of a compute unit's LDS in flight. (Loads straight into the MFMA operand
+// registers take twice the time: adjacent lanes then read different rows, and the
+// address unit takes one lane per clock instead of four. Eight waves measured
+// 0-10 % slower than four.) At the end the waves' sums meet in LDS and are added
+// in order. Against the tile kernels with a split reduction and its reducing
+// launch: 24 tokens x 2,048 x 22,016 with the activation 28.0 -> 20.9 us (4.3 TB/s
+// of weights), 11,008 x 2,048 22.0 -> 15.4 us (X, read by every workgroup, bounds
+// it), 2,048 x 2,048 kernel time 12.5 -> 4.3 us; 1 token 25.4 -> 22.3, 20.5 ->
+// 11.3, 10.6 -> 4.0 us.
+constexpr int kRowsWaves = 4;
+
+template <int XT, int G, int WR, bool kAct>
+__global__ __launch_bounds__(64 * kRowsWaves, 1) void gateup_rows_kernel(GemmArgs a) {
+  constexpr int NW = kRowsWaves;
+  constexpr int kSlot = (G * WR + XT * 16) * kRow;        // bytes of a chunk
+  constexpr int kMoves = (G * WR + XT * 16) / 8;          // its transfers
+  // With one weight-row tile the block sums of up to kOrdered blocks are kept beside
+  // the rings and added in order; otherwise the waves' totals take the rings' place.
+  constexpr int kOrdered = G == 1 ? 8 : 0;
+  constexpr int kSumBytes = (G == 1 ? kOrdered : NW) * G * XT * 1024;
+  constexpr int kRoom = kSmem - (G == 1 ? kSumBytes : 0);
+  constexpr int kSlots = kRoom / NW / kSlot < 4 ? kRoom / NW / kSlot : 4;
+  constexpr int kRings = NW * kSlots * kSlot;
+  constexpr int kBytes = G == 1 ? kRings + kSumBytes : kRings > kSumBytes ? kRings : kSumBytes;
+  static_assert(kSlots >= 2 && kBytes <= kSmem, "at least two chunks per wave; the sums fit");
+  static_assert(!kAct || G % 2 == 0, "gate and up rows in pairs");
+  __shared__ __attribute__((aligned(1024))) char smem[kBytes];
+#ifdef __HIP_DEVICE_COMPILE__
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r16 = lane & 15, q = lane >> 4;
+  const int m0 = blockIdx.y * 16 * XT;
+  const int c0 = blockIdx.x * (kAct ? WR / 2 : WR) * G;   // first column (feature) of the tile
+  constexpr int kGP = kAct ? G / 2 : G;                   // weight-row tiles per weight half
+  const int ncols = kAct ? a.I : a.N2;
+
+  Rows rw[2], rx;
+  rw[0].set(a.w, c0, ncols, WR * kGP, a.H);
+  rw[1].set(a.w + (kAct ? size_t(a.I) * a.H : 0), c0, ncols, WR * kGP, a.H);
+  rx.set(a.x, m0, a.T, 16 * XT, a.H);
+  const uint32_t pitch = uint32_t(a.H) * 2;
+  // transfer i of a tile: rows 8 i + L / 8, swizzled as in the tile kernels
+  uint32_t off[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int r = 8 * i + lane / 8;
+    off[i] = uint32_t(r) * pitch + 16 * ((lane & 7) ^ ((r >> 1) & 7));
+  }
+  const int nchunks = a.H / kBK;
+  char* ring = smem + w * kSlots * kSlot;
+  auto load = [&](int slot, int c) {
+    char* dst = ring + slot * kSlot;
+    const uint32_t so = uint32_t(c) * kRow;
+#pragma unroll
+    for (int t = 0; t < XT; ++t)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        transfer(rx, dst + t * 16 * kRow + i * 1024, off[i] + uint32_t(16 * t) * pitch, so);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int i = 0; i < WR / 8; ++i)
+        transfer(rw[g / kGP], dst + (XT * 16 + g * WR) * kRow + i * 1024, off[i] + uint32_t(WR * (g % kGP)) * pitch, so);
+  };
+  // a tile of eight weight rows fills the MFMA's 16 twice; the second half is dropped
+  int frag_x[2], frag_w[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int r = r16 % WR;
+    frag_x[j] = r16 * kRow + 16 * ((4 * j + q) ^ ((r16 >> 1) & 7));
+    frag_w[j] = r * kRow + 16 * ((4 * j + q) ^ ((r >> 1) & 7));
+  }
+
+  // Two-level sums, as in the tile kernels. In order: blocks of four chunks, wave w
+  // taking blocks w, w + NW, ...; otherwise blocks of eight of the wave's chunks
+  // w, w + NW, ...
+  f32x4 acc[G][XT], total[G][XT];
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int t = 0; t < XT; ++t) total[g][t] = acc[g][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4* sums = reinterpret_cast<f32x4*>(smem + (G == 1 ? kRings : 0));   // [blocks or waves][G * XT][64]
+  const int nblocks = (nchunks + 3) / 4;
+  const bool ordered = nblocks <= kOrdered;
+  auto end_block = [&](int blk) {
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int t = 0; t < XT; ++t) {
+        if (ordered)
+          sums[(blk * G * XT + g * XT + t) * 64 + lane] = acc[g][t];
+        else
+          total[g][t] += acc[g][t];
+        acc[g][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+  };
+  // the i-th chunk of this wave; neighbouring chunks are read together where the
+  // order allows it (2-3 us faster on wide outputs)
+  auto chunk_of = [&](int i) { return ordered ? 4 * (w + NW * (i >> 2)) + (i & 3) : w + NW * i; };
+  int n = w < nchunks ? (nchunks - 1 - w) / NW + 1 : 0;                    // chunks of this wave
+  if (ordered) {
+    const int mine = w < nblocks ? (nblocks - 1 - w) / NW + 1 : 0;
+    // only the last block of all may be short
+    n = mine == 0 ? 0 : 4 * mine - ((w + NW * (mine - 1) == nblocks - 1) ? 4 * nblocks - nchunks : 0);
+  }
+  if (n > 0) {
+    // past its last chunk a wave fetches that one again, so that every wait counts
+    // the same number of younger transfers
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s) load(s, chunk_of(min(s, n - 1)));
+    int slot = 0;
+    for (int i = 0; i < n; ++i) {
+      wait_vmcnt<kMoves * (kSlots - 1)>();
+      asm volatile("" ::: "memory");
+      const char* src = ring + slot * kSlot;
+      bf16x8 fx[XT][2], fw[G][2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+#pragma unroll
+        for (int t = 0; t < XT; ++t) fx[t][j] = as_bf16x8(lds16(src + t * 16 * kRow + frag_x[j]));
+#pragma unroll
+        for (int g = 0; g < G; ++g) fw[g][j] = as_bf16x8(lds16(src + (XT * 16 + g * WR) * kRow + frag_w[j]));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(0xC07F);   // the chunk is in registers before its slot is refilled
+      asm volatile("" ::: "memory");
+      load(slot, chunk_of(min(i + kSlots, n - 1)));
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int t = 0; t < XT; ++t)
+#pragma unroll
+          for (int g = 0; g < G; ++g)
+            acc[g][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[g][j], fx[t][j], acc[g][t], 0, 0, 0);
+      slot = slot + 1 == kSlots ? 0 : slot + 1;
+      if ((i & (ordered ? 3 : 7)) == (ordered ? 3 : 7) || i + 1 == n) end_block(w + NW * (i >> 2));
+    }
+  }
+  wait_vmcnt<0>();
+  if (G > 1) __syncthreads();               // every ring is idle before the sums take its place
+  if (!ordered) {
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int t = 0; t < XT; ++t) sums[(w * G * XT + g * XT + t) * 64 + lane] = total[g][t];
+  }
+  __syncthreads();
+  const int nsums = ordered ? nblocks : NW;
+  // wave w finishes results w, w + NW, ...: lane L holds token row L % 16, columns
+  // 4 (L / 16) .. + 3
+  for (int f = w; f < kGP * XT; f += NW) {
+    f32x4 s = sums[f * 64 + lane];
+    for (int v = 1; v < nsums; ++v) s += sums[(v * G * XT + f) * 64 + lane];
+    if constexpr (kAct) {
+      f32x4 u = sums[(kGP * XT + f) * 64 + lane];
+      for (int v = 1; v < nsums; ++v) u += sums[(v * G * XT + kGP * XT + f) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[e] = silu_f32(s[e]) * u[e];
+    }
+    const int m = m0 + 16 * (f % XT) + r16, c = c0 + WR * (f / XT) + 4 * q;
+    if (m >= a.T || 4 * q >= WR) continue;
+    uint16_t* dst = a.y + size_t(m) * ncols + c;
+    if (c + 4 <= ncols) {
+      u32x2 v;
+      v[0] = pack_bf16x2(s[0], s[1]);
+      v[1] = pack_bf16x2(s[2], s[3]);
+      *reinterpret_cast<u32x2*>(dst) = v;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (c + e < ncols) dst[e] = uint16_t(pack_bf16x2(s[e], 0.f) & 0xffff);
+    }
+  }
+#endif
+}
+
+template <int G, int WR, bool kAct>
+void launch_rows(const GemmArgs& a, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  const int ncols = kAct ? a.I : a.N2, per = (kAct ? WR / 2 : WR) * G;
+  const int xt = a.T <= 16 ? 1 : a.T <= 32 ? 2 : 4;
+  const dim3 grid(unsigned((ncols + per - 1) / per), unsigned((a.T + 16 * xt - 1) / (16 * xt))), block(64 * kRowsWaves);
+  if (xt == 1)
+    hipExtLaunchKernelGGL((gateup_rows_kernel<1, G, WR, kAct>), grid, block, 0, stream, ev_start, ev_stop, 0, a);
+  else if (xt == 2)
+    hipExtLaunchKernelGGL((gateup_rows_kernel<2, G, WR, kAct>), grid, block, 0, stream, ev_start, ev_stop, 0, a);
+  else
+    hipExtLaunchKernelGGL((gateup_rows_kernel<4, G, WR, kAct>), grid, block, 0, stream, ev_start, ev_stop, 0, a);
 }
 
 // y = bf16(sum over splits of the partials), the splits summed in order; thread i
@@ -668,6 +893,35 @@ Shape shape_cost(int32_t T, int32_t H, int32_t N2, int grid_max, int bm, int spl
   return s;
 }
 
+// The few-row kernel's variants: weight-row tiles per workgroup and their rows.
+// One eight-row tile doubles the workgroups where the columns are few.
+struct RowsShape {
+  int g, wr;
+  bool with_act, without;
+};
+constexpr RowsShape kRowsShapes[] = {{1, 8, false, true}, {1, 16, false, true}, {2, 8, true, false},
+                                     {2, 16, true, true}, {4, 16, true, true},  {6, 16, true, true}};
+constexpr int kRowsMaxT = 256;   // measured up to here; from about 64 rows the tiles win on wide outputs
+
+// Microseconds: the weights stream at 5.8 TB/s over the chip or 110 GB/s into one
+// compute unit, X (from L2) at 114 GB/s, one after the other; the rest is the
+// launch and the workgroup's fill and final sums. Fitted with kTilesBase, the
+// launches of a call of the tile kernels, to 460 timed calls (1 to 256 tokens, ten
+// projections; 13 % rms), over which the choice is 0.7 % slower than the best.
+constexpr double kTilesBase = 7.5;
+double rows_cost(int32_t T, int32_t H, int32_t N2, int cus, const RowsShape& v) {
+  const int xt = T <= 16 ? 1 : T <= 32 ? 2 : 4;
+  const double cols = double((int64_t(N2) + v.g * v.wr - 1) / (v.g * v.wr));
+  const double mt = (T + 16 * xt - 1) / (16 * xt);
+  const int slot = (v.g * v.wr + 16 * xt) * kRow;
+  const int ring = 4 * slot * std::min(4, kSmem / 4 / slot);
+  const int per_cu = std::max(1, kSmem / std::max(ring, 4 * v.g * xt * 1024));
+  const double wgs = cols * mt, room = double(cus) * per_cu;
+  const double rounds = wgs > room ? std::ceil(wgs / room) * per_cu : std::max(1.0, wgs / cus);
+  const double w = 2.0 * v.g * v.wr * H, x = 2.0 * std::min(T, 16 * xt) * H;
+  return 2.4 + std::max(rounds * w / 1.1e5, mt * 2.0 * N2 * H / 5.8e6) + rounds * x / 1.14e5 + 0.11 * v.g * xt;
+}
+
 }  // namespace
 
 int64_t gateup_tiles(int32_t T, int32_t N2) {
@@ -701,9 +955,16 @@ hipError_t launch_gateup(const uint16_t* x, const uint16_t* w, uint16_t* y, int3
     // one workgroup per compute unit (a multiple of 8, so that each stays on one XCD's
     // share of the tiles)
     const int grid_max = std::max(8, cus / 8 * 8);
+    // Narrow outputs (the K and V projections, whose results are cached) are summed
+    // in 256-feature blocks added in order, whatever the tiles: by blocks of four
+    // stages, or by the full split into such blocks. The result then does not depend
+    // on the number of tokens beside it. Wider outputs take the cheapest split.
+    const bool narrow = !act && N2 <= 2 * kBN;
+    const int full = gateup_splits(T, H, N2, cus);
     Shape best;
     for (int bm : {256, 128, 64})
       for (int s = 1; s <= max_splits; ++s) {
+        if (narrow && ((s > 1 && s != full) || (bm == 256 && T >= 256))) continue;
         const Shape c = shape_cost(T, H, N2, grid_max, bm, s);
         if (c.items > INT32_MAX / 2) continue;
         if (best.bm == 0 || c.cost < best.cost) best = c;
@@ -725,6 +986,43 @@ hipError_t launch_gateup(const uint16_t* x, const uint16_t* w, uint16_t* y, int3
     a.tail_m = best.tail_m;
     a.splits = splits;
     a.light = best.light;
+    a.block = narrow ? 4 : 8;
+    if (T <= kRowsMaxT) {
+      const RowsShape* rows = nullptr;
+      double cost = best.cost + kTilesBase;
+      for (const RowsShape& v : kRowsShapes) {
+        if (!(act ? v.with_act : v.without) || N2 / (v.g * v.wr) >= (1 << 22) || (narrow && v.g > 1)) continue;
+        const double c = rows_cost(T, H, N2, grid_max, v);
+        if (c < cost) {
+          cost = c;
+          rows = &v;
+        }
+      }
+      if (rows) {
+        if (act) {
+          if (rows->wr == 8)
+            launch_rows<2, 8, true>(a, stream, ev_start, ev_stop);
+          else if (rows->g == 2)
+            launch_rows<2, 16, true>(a, stream, ev_start, ev_stop);
+          else if (rows->g == 4)
+            launch_rows<4, 16, true>(a, stream, ev_start, ev_stop);
+          else
+            launch_rows<6, 16, true>(a, stream, ev_start, ev_stop);
+        } else {
+          if (rows->wr == 8)
+            launch_rows<1, 8, false>(a, stream, ev_start, ev_stop);
+          else if (rows->g == 1)
+            launch_rows<1, 16, false>(a, stream, ev_start, ev_stop);
+          else if (rows->g == 2)
+            launch_rows<2, 16, false>(a, stream, ev_start, ev_stop);
+          else if (rows->g == 4)
+            launch_rows<4, 16, false>(a, stream, ev_start, ev_stop);
+          else
+            launch_rows<6, 16, false>(a, stream, ev_start, ev_stop);
+        }
+        return hipGetLastError();
+      }
+    }
     const dim3 grid(unsigned(std::min<int64_t>(best.items, grid_max)));
     hipEvent_t ev = splits > 1 ? nullptr : ev_stop;
     if (best.bm == 256) {

@@ -155,3 +155,27 @@ def test_operands_off_the_16_byte_grid(lib, which):
     y = torch.full((T, N), float("nan"), dtype=torch.bfloat16, device="cuda")
     ppas.gateup_proj(x, w, y)
     check(f64(lib, y), xb, wb, label=f"{which} off by 8 bytes")
+
+
+@pytest.mark.parametrize("T,H,N", [
+    # few rows: 16-, 32- and 64-row tiles and their edges, several of them; one to six weight-row tiles per
+    # workgroup; a last block of one chunk; fewer chunks than waves; more blocks than are kept in order
+    (1, 2048, 22016), (16, 2048, 2050), (17, 64, 300), (24, 11008, 2048), (33, 576, 256), (48, 2048, 11010),
+    (64, 128, 40), (65, 2048, 2048), (100, 2112, 130), (256, 2048, 250), (20, 192, 9001)])
+def test_few_rows_every_element(lib, T, H, N):
+    print(f"gate-up rows T={T} H={H} N={N}", flush=True)
+    xb = I.gateup_tokens(9, T, 0, hidden=H)
+    wb = I.gateup_weight(9, hidden=H, inter=(N + 1) // 2)[:N]
+    check(f64(lib, run(lib, xb, wb)), xb, wb, label=f"T{T} H{H} N{N}")
+
+
+def test_narrow_output_does_not_depend_on_the_rows_beside_it(lib):
+    """The K and V projections (up to 512 columns) add the same 256-feature block sums in
+    the same order in every kernel: a row's bits are the same in calls of any size."""
+    ppas, step, torch = lib
+    wb = I.gateup_weight(10, hidden=2048, inter=128)
+    xb = I.gateup_tokens(10, 2500, 0, hidden=2048)
+    whole = run(lib, xb, wb)
+    for n in (1, 16, 40, 200, 256, 300, 700, 1100):
+        part = run(lib, xb[:n], wb)
+        assert torch.equal(part.view(torch.int16), whole[:n].view(torch.int16)), n

@@ -135,3 +135,13 @@ def test_tile_shapes_every_element(lib, T, H, NI):
     xb = I.gateup_tokens(8, T, 0, hidden=H)
     wb = I.gateup_weight(8, hidden=H, inter=NI)
     check(f64(run(lib, xb, wb)), xb, wb, label=f"act T{T} H{H} I{NI}")
+
+
+@pytest.mark.parametrize("T,H,NI", [(1, 2048, 11008), (16, 64, 500), (17, 1024, 3001), (24, 2048, 5504),
+                                    (64, 576, 1500), (65, 128, 700), (200, 2048, 640)])
+def test_few_rows_every_element(lib, T, H, NI):
+    """Few rows: tiles of 16, 32 and 64 rows and two to six weight-row tiles per workgroup."""
+    print(f"gate-up-act rows T={T} H={H} I={NI}", flush=True)
+    xb = I.gateup_tokens(11, T, 0, hidden=H)
+    wb = I.gateup_weight(11, hidden=H, inter=NI)
+    check(f64(run(lib, xb, wb)), xb, wb, label=f"act T{T} H{H} I{NI}")
