@@ -48,9 +48,10 @@ struct StepArgs {
 };
 
 // The kernel comes in two shapes, by waves per workgroup W: W = 4 (prefill tiles
-// of 16 positions, two workgroups per CU) and W = 8 (tiles of 32 positions, one
-// workgroup per CU; each staged K/V byte then serves 256 rows). The planner
-// picks one per step.
+// of 16 positions, two workgroups per CU, which fill each other's waits) and W = 8
+// (tiles of 32 positions, one workgroup per CU, whose two halves take turns on the
+// matrix cores; each staged K/V byte then serves 256 rows). The planner picks one
+// per step.
 template <int kW>
 constexpr int threads_of() { return 64 * kW; }
 constexpr int kRegion = 1024;              // one wave's 64 x 16-byte LDS transfer
@@ -121,10 +122,11 @@ __device__ __forceinline__ u32x4 keep_first(u32x4 v, int first, int lim) {
 }
 
 // ---------------------------------------------------------------------------
-// Prefill tile: 4W positions x 8 query heads = 32W rows; wave w owns positions
-// 4w..4w+3 (32 rows, one per lane column n = lane & 31; lanes n and n+32 share
-// a row). All W waves read the same staged K/V blocks. S^T = K Q^T and O^T += V^T P^T on 32x32x16 MFMAs, so every softmax
-// reduction stays inside a lane plus one exchange across the two half-waves.
+// Prefill tile of the four-wave shape: 16 positions x 8 query heads = 128 rows; wave
+// w owns positions 4w..4w+3 (32 rows, one per lane column n = lane & 31; lanes n and
+// n+32 share a row). All waves read the same staged K/V blocks. S^T = K Q^T and
+// O^T += V^T P^T on 32x32x16 MFMAs, so every softmax reduction stays inside a lane
+// plus one exchange across the two half-waves.
 //
 // MFMA row m of a 32-key tile reads key pi(m), which swaps the middle two groups
 // of 4 in each 16, so that half-wave h ends up holding keys 16s+8h..16s+8h+7 of
@@ -132,7 +134,7 @@ __device__ __forceinline__ u32x4 keep_first(u32x4 v, int first, int lim) {
 //
 // LDS holds each 64-key block in MFMA operand order, written straight from
 // global memory by 16-byte LDS transfers (16 regions of K and 16 of V per block,
-// 16/W of each per wave): K region (t, j) = 8t + j holds, at
+// four of each per wave): K region (t, j) = 8t + j holds, at
 // 16 L, lane L's A chunk for key tile t and k-step j (key 32t + pi(L & 31),
 // features 16j + 8(L >> 5) .. +7); V region (tt, s) = 4tt + s holds lane L's V^T
 // chunk (feature 32tt + (L & 31), keys 16s + 8(L >> 5) .. +7). Every operand
@@ -166,37 +168,24 @@ __device__ __forceinline__ PageIds page_ids(const PrefillCtx& c, int blk) {
   return r;
 }
 
-// This wave's K transfers of a block: regions R w .. R w + R-1 (R = 16/W), all in
-// key tile t = R w / 8 (pages 2t and 2t+1 of the block), k-steps (R w mod 8) + i.
-template <int kW>
+// This wave's K transfers of a block: regions 4w .. 4w + 3, all in key tile t = w / 2
+// (pages 2t and 2t+1 of the block), k-steps 4 (w mod 2) + i.
 __device__ __forceinline__ void dma_k(const PrefillCtx& c, const PageIds& pg, char* kbuf) {
-  constexpr int R = 16 / kW;
-  const bool t1 = (R * c.w) >> 3;
+  const bool t1 = c.w >> 1;
   const int lo = t1 ? pg.p[2] : pg.p[0];
   const int hi = t1 ? pg.p[3] : pg.p[1];
   const uint16_t* lo_base = c.a->kp + size_t(lo) * c.page_stride;
   const uint16_t* hi_base = c.a->kp + size_t(hi) * c.page_stride;
   const uint16_t* base = ((c.pi_n >> 4) ? hi_base : lo_base) + c.k_lane_off;
 #pragma unroll
-  for (int i = 0; i < R; ++i) dma16(base + 2 * i * kChunkElems, kbuf + (R * c.w + i) * kRegion);
+  for (int i = 0; i < 4; ++i) dma16(base + 2 * i * kChunkElems, kbuf + (4 * c.w + i) * kRegion);
 }
 
-// This wave's V transfers of a block: regions R w .. R w + R-1, all in feature
-// tile tt = R w / 4, over pages s = (R w mod 4) + i of the block.
-template <int kW>
+// This wave's V transfers of a block: regions 4w .. 4w + 3, feature tile w, page s.
 __device__ __forceinline__ void dma_v(const PrefillCtx& c, const PageIds& pg, char* vbuf) {
-  constexpr int R = 16 / kW;
-  if constexpr (R == 4) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
-      dma16(c.a->vp + size_t(pg.p[s]) * c.page_stride + c.v_lane_off, vbuf + (4 * c.w + s) * kRegion);
-  } else {
-    static_assert(R == 2, "four or eight waves");
-    const int p0 = (c.w & 1) ? pg.p[2] : pg.p[0];
-    const int p1 = (c.w & 1) ? pg.p[3] : pg.p[1];
-    dma16(c.a->vp + size_t(p0) * c.page_stride + c.v_lane_off, vbuf + (2 * c.w) * kRegion);
-    dma16(c.a->vp + size_t(p1) * c.page_stride + c.v_lane_off, vbuf + (2 * c.w + 1) * kRegion);
-  }
+  for (int s = 0; s < 4; ++s)
+    dma16(c.a->vp + size_t(pg.p[s]) * c.page_stride + c.v_lane_off, vbuf + (4 * c.w + s) * kRegion);
 }
 
 __device__ __forceinline__ void qk_block(const char* kbuf, int lane, const bf16x8 (&qf)[8], f32x16 (&S)[2]) {
@@ -255,18 +244,12 @@ __device__ __forceinline__ void pv_block(const char* vbuf, int lane, int h, cons
     }
 }
 
-template <int kW>
 __device__ __forceinline__ void prefill_tile(const StepArgs& a, const WorkItem& it, char* smem) {
-  constexpr int R = 16 / kW;   // transfers of K (and of V) per wave per block
   const int tid = threadIdx.x;
   PrefillCtx c;
   c.a = &a;
   c.lane = tid & 63;
-  // In the eight-wave shape the wave index is declared wave-uniform, so the page
-  // selects and page bases of the LDS transfers stay on the scalar unit (16 % fewer
-  // vector instructions in the main loop, ~1 % faster); the four-wave shape measured
-  // ~1 % slower that way and keeps the per-lane form.
-  c.w = kW == 8 ? int(__builtin_amdgcn_readfirstlane(tid >> 6)) : tid >> 6;
+  c.w = tid >> 6;   // left per lane: declared wave-uniform it measured ~1 % slower here
   c.n = c.lane & 31;
   c.h = c.lane >> 5;
   {
@@ -278,10 +261,10 @@ __device__ __forceinline__ void prefill_tile(const StepArgs& a, const WorkItem& 
   c.page_stride = size_t(a.hkv) * kPageElems;
   {
     const uint32_t head_off = uint32_t(it.kvh) * kPageElems;
-    // K: chunk 2j + h of k-step j = (R w mod 8) + i, slot pi(n) & 15
-    c.k_lane_off = head_off + (2 * ((R * c.w) & 7) + c.h) * kChunkElems + (c.pi_n & 15) * 8;
-    // V: feature 32 tt + n with tt = R w / 4, slots 8h..8h+7
-    c.v_lane_off = head_off + (32 * ((R * c.w) >> 2) + c.n) * kPage + 8 * c.h;
+    // K: chunk 2j + h of k-step j = 4 (w mod 2) + i, slot pi(n) & 15
+    c.k_lane_off = head_off + (8 * (c.w & 1) + c.h) * kChunkElems + (c.pi_n & 15) * 8;
+    // V: feature 32 w + n, slots 8h..8h+7
+    c.v_lane_off = head_off + (32 * c.w + c.n) * kPage + 8 * c.h;
   }
   c.key_lo = it.key_lo;
   c.kend = it.key_hi;
@@ -320,9 +303,9 @@ __device__ __forceinline__ void prefill_tile(const StepArgs& a, const WorkItem& 
   // prologue: K(0), K(1), V(0) in flight; page ids of blocks 1 and 2 kept for the loop
   const PageIds pg0 = page_ids(c, 0);
   PageIds pg1 = page_ids(c, 1), pg2 = page_ids(c, 2);
-  dma_k<kW>(c, pg0, kbuf(0));
-  dma_k<kW>(c, pg1, kbuf(1));
-  dma_v<kW>(c, pg0, vbuf(0));
+  dma_k(c, pg0, kbuf(0));
+  dma_k(c, pg1, kbuf(1));
+  dma_v(c, pg0, vbuf(0));
   wait_vmem();
   __syncthreads();
 
@@ -332,8 +315,8 @@ __device__ __forceinline__ void prefill_tile(const StepArgs& a, const WorkItem& 
 
   // Main loop: blocks b and b + 1 both unmasked.
   auto main_iter = [&](int b, f32x16 (&Scur)[2], f32x16 (&Snext)[2]) {
-    dma_k<kW>(c, pg2, kbuf(b));
-    dma_v<kW>(c, pg1, vbuf(b + 1));
+    dma_k(c, pg2, kbuf(b));
+    dma_v(c, pg1, vbuf(b + 1));
     pg1 = pg2;
     pg2 = page_ids(c, b + 3);
     const float m_use = (m_run == kNegInf) ? 0.f : m_run;
@@ -373,8 +356,8 @@ __device__ __forceinline__ void prefill_tile(const StepArgs& a, const WorkItem& 
         }
       rescale_if_grown(block_max(SA) * sl2, m_run, l_run, O);
     }
-    if (b + 2 < nblk) dma_k<kW>(c, pg2, kbuf(b));
-    if (b + 1 < nblk) dma_v<kW>(c, pg1, vbuf(b + 1));
+    if (b + 2 < nblk) dma_k(c, pg2, kbuf(b));
+    if (b + 1 < nblk) dma_v(c, pg1, vbuf(b + 1));
     pg1 = pg2;
     pg2 = page_ids(c, b + 3);
     const float m_use = (m_run == kNegInf) ? 0.f : m_run;
@@ -419,6 +402,356 @@ __device__ __forceinline__ void prefill_tile(const StepArgs& a, const WorkItem& 
       }
     if (c.h == 0) a.part_ml[slot] = make_float2(m_run, l_tot);
   }
+}
+
+// ---------------------------------------------------------------------------
+// Prefill tile of the eight-wave shape: 32 positions x 8 query heads = 256 rows,
+// 32 per wave (position 4w + 2u + n / 8, head n % 8 for row tile u and lane column
+// n = lane & 15), on 16x16x32 MFMAs, S^T = K Q^T and O^T += V^T P^T.
+//
+// What bounds it: per 64-key block a wave's MFMAs take 1,024 clocks of its SIMD, its
+// softmax about as many vector clocks, and the eight waves' operand reads 2,048
+// clocks of LDS at 128 B per clock, so the three have to overlap. Waves 0-3 and 4-7
+// (one of each per SIMD) therefore run half an iteration apart: while one half
+// issues the MFMAs of a block (QK^T of block t, PV of block t - 1), the other
+// exponentiates, and a workgroup barrier swaps them. K fragments are read during the
+// softmax, V fragments under the QK^T MFMAs, into the registers that K leaves.
+// 16x16x32 MFMAs cost the chip less power than 32x32x16 ones on ordinary values
+// (2.07 against 1.83 PFLOP/s from registers). The matrix cores are busy 55 % of the
+// clocks; the softmax half is the longer one (1,800 clocks against 1,150 when both
+// run, as vector and matrix instructions share the SIMD's issue), and the chip clocks
+// at 2.1 GHz under this load.
+//
+// Measured on one 16,384-position chunk behind 8,616 cached ones, 32/4 heads: 1,816 us
+// against 1,962 us for the same tile with all waves in step (which left the overlap to
+// chance). Also measured: reading V and K in the matrix half only, 2,000 us; 32x32x16
+// MFMAs on this schedule, 1,990 us.
+//
+// LDS holds the pages of a block one by one, 4 KB of K and 4 KB of V, so a transfer
+// copies 1 KB of one page, its page id and base are scalar, and the waits count LDS
+// reads exactly.
+//
+// Order: a half-iteration is the span between two barriers. Waves 0-3 run the matrix
+// part of block t in 2t and its softmax in 2t + 1; waves 4-7 one later. Set x of the
+// transfers (K of block x + 3, V of block x + 2) is issued by the early waves in
+// 2x + 1, by the late ones in 2x; both have waited for set x by the end of 2x + 4,
+// where K of block x + 3 is first read in 2x + 5 and V of block x + 2 in 2x + 6. The
+// buffers that set x overwrites (K of block x - 1, V of block x - 2) were last read in
+// 2x - 1, by the late waves' matrix part of block x - 1.
+// ---------------------------------------------------------------------------
+constexpr int kPPRing = 4;   // blocks of K, and of V, in LDS
+__device__ __forceinline__ void prefill_pp(const StepArgs& a, const WorkItem& it, char* smem) {
+#ifdef __HIP_DEVICE_COMPILE__
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool late = w >= 4;
+  const int n = lane & 15, q = lane >> 4;
+  const int npos = it.npos_kind & 0xffff;
+  const int key_lo = it.key_lo, kend = it.key_hi;
+  const int nblk = (kend - key_lo + kPrefillBlock - 1) / kPrefillBlock;
+  // blocks 0..nfull-1 lie wholly at or below the tile's first position
+  const int nfull = min(nblk, (it.pos0 + 1 - key_lo) >> 6);
+  const float sl2 = a.scale_log2;
+
+  int pl[2];
+  bool rvalid[2];
+  bf16x8 qf[2][4];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    pl[u] = 4 * w + 2 * u + (n >> 3);
+    rvalid[u] = pl[u] < npos;
+    const uint16_t* qrow =
+        a.q + (size_t(it.row0 + (rvalid[u] ? pl[u] : 0)) * a.hq + it.kvh * kGroup + (n & 7)) * kHeadDim + 8 * q;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) qf[u][j] = as_bf16x8(rvalid[u] ? ldg16(qrow + 32 * j) : u32x4{0, 0, 0, 0});
+  }
+
+  // This wave's share of a block's transfers: page w / 2 of the four, the first or
+  // second 2 KB of its K and of its V. Lane i of `pid` holds that page's id in block
+  // pid0 + i (past the item's last page, that page again).
+  const int32_t* btrow = a.bt + size_t(it.seq) * a.bt_stride;
+  const int first_page = key_lo >> 4, last_page = (kend - 1) >> 4;
+  int pid = 0, pid0 = 0;
+  auto load_pids = [&](int b0) {
+    pid0 = b0;
+    pid = btrow[min(first_page + 4 * (b0 + lane) + (w >> 1), last_page)];
+    asm volatile("" ::"v"(pid));   // complete here, so that no wait is left for the loop
+  };
+  const uint32_t page_bytes = uint32_t(a.hkv) * kPageElems * 2;
+  const uint32_t part_off = uint32_t(it.kvh) * kPageElems * 2 + (w & 1) * 2048;
+  // odd pages keep K's slots in the order s ^ 4, and every 16 features of V keep their
+  // first and their second eight slots apart (256 bytes each): operand reads then hit
+  // every bank once
+  const int k_lane = 256 * q + 16 * (n ^ (4 * ((w >> 1) & 1)));
+  const int v_lane = 32 * (16 * (lane >> 5) + n) + 16 * (q & 1);
+
+  // Set x of a wave's transfers is K of block x + kPPRing - 1 and V of block x +
+  // kPPRing - 2, two transfers each, issued one by one (`move`).
+  struct Source {
+    uint32_t lo, hi;
+  };
+  auto source = [&](const uint16_t* pool, int page) {
+    const uint64_t b = reinterpret_cast<uint64_t>(pool) + uint64_t(uint32_t(page)) * page_bytes + part_off;
+    return Source{uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(b))),
+                  uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(b >> 32)))};
+  };
+  auto move1 = [&](const Source& s, char* dst, int i, int lane_off) {
+    __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<void*>(uint64_t(s.lo) | (uint64_t(s.hi) << 32)), 0, 2048, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(d, (lds_void*)(dst + i * 1024), 16, lane_off, i * 1024, 0, 0);
+  };
+  const int share = (w >> 1) * 4096 + (w & 1) * 2048;
+  int pg_next = 0;     // id of this wave's page in the block whose V comes next
+  int kb_next = 0;     // the block whose K comes next
+  int ks = 0, vs = 0;  // ring slots they go to
+  Source ksrc, vsrc;
+  auto aim_k = [&]() {
+    if (kb_next - pid0 >= 64) load_pids(kb_next);
+    pg_next = __builtin_amdgcn_readlane(pid, kb_next - pid0);
+    ++kb_next;
+    ksrc = source(a.kp, pg_next);
+  };
+  auto aim = [&]() {   // the next set's addresses
+    vsrc = source(a.vp, pg_next);
+    aim_k();
+  };
+  auto move = [&](int i) {
+    if (i < 2) {
+      move1(vsrc, smem + (kPPRing + vs) * kBlockBytes + share, i, v_lane);
+      if (i == 1) vs = vs + 1 == kPPRing ? 0 : vs + 1;
+    } else {
+      move1(ksrc, smem + ks * kBlockBytes + share, i - 2, k_lane);
+      if (i == 3) ks = ks + 1 == kPPRing ? 0 : ks + 1;
+    }
+  };
+  auto move_all = [&]() {
+    aim();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) move(i);
+  };
+
+  f32x4 O[8][2], S[4][2];
+#pragma unroll
+  for (int ft = 0; ft < 8; ++ft)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) O[ft][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run[2] = {kNegInf, kNegInf}, l_run[2] = {0.f, 0.f};
+  u32x4 pk[2][2];      // [u][s]: probabilities as the PV operand of 32 keys
+  bf16x8 kf[4][4];     // [page][32 features]
+
+  // K fragment (tile kt = 2s + t, k-step j): MFMA row m reads key 32s + 8(m / 4) + 4t + m % 4
+  // of the block, so that lane (n, q) ends up with keys 32s + 8q .. + 7, in order over the
+  // two tiles of s: the 16 bytes of its V fragment.
+  int kat[2], vat;     // this lane's next K reads (t = 0, 1) and V reads
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int slot = 8 * ((n >> 2) & 1) + 4 * t + (n & 3);
+    kat[t] = (n >> 3) * 4096 + q * 256 + 16 * (slot ^ (4 * (n >> 3)));
+  }
+  vat = kPPRing * kBlockBytes + (q >> 1) * 4096 + (q & 1) * 256 + 16 * n;
+  int kr = 0, vr = 0;  // ring slots they are in
+  auto read_k_step = [&](int j) {
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) kf[kt][j] = as_bf16x8(lds16(smem + kat[kt & 1] + 8192 * (kt >> 1) + 1024 * j));
+  };
+  auto next_k = [&]() {
+    const int step = kr + 1 == kPPRing ? -(kPPRing - 1) * kBlockBytes : kBlockBytes;
+    kr = kr + 1 == kPPRing ? 0 : kr + 1;
+    kat[0] += step;
+    kat[1] += step;
+  };
+  auto next_v = [&]() {
+    vat += vr + 1 == kPPRing ? -(kPPRing - 1) * kBlockBytes : kBlockBytes;
+    vr = vr + 1 == kPPRing ? 0 : vr + 1;
+  };
+  auto read_v = [&](int s, int ft) { return lds16(smem + vat + 8192 * s + 512 * ft); };
+  auto qk_step = [&](int j) {
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        S[kt][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kt][j], qf[u][j], j == 0 ? zero : S[kt][u], 0, 0, 0);
+      }
+  };
+  auto pv_step = [&](int s, int ft, u32x4 vf) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      O[ft][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vf), as_bf16x8(pk[u][s]), O[ft][u], 0, 0, 0);
+  };
+  // QK^T of block t and PV of block t - 1
+  auto matrix_part = [&](bool pv) {
+    u32x4 vf[2][8];
+    auto fetch_v = [&](int g) {   // a quarter of the V fragments
+      if (pv) {
+#pragma unroll
+        for (int ft = 4 * (g & 1); ft < 4 * (g & 1) + 4; ++ft) vf[g >> 1][ft] = read_v(g >> 1, ft);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // each step's operands are read into the registers that an earlier step leaves
+    qk_step(0);
+    __builtin_amdgcn_sched_barrier(0);
+    read_k_step(3);
+    next_k();
+    __builtin_amdgcn_sched_barrier(0);
+    qk_step(1);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_v(0);
+    qk_step(2);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_v(1);
+    qk_step(3);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_v(2);
+    fetch_v(3);
+    if (pv) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int ft = 0; ft < 8; ++ft) pv_step(s, ft, vf[s][ft]);
+      next_v();
+    }
+  };
+  // Softmax of block b (S -> pk), with K of the next block read under it. A row's
+  // maximum is only gathered from its four lanes when one of them has outgrown the
+  // running one by more than kSlack.
+  auto vector_part = [&](int b) {
+    read_k_step(0);
+    read_k_step(1);
+    read_k_step(2);
+    __builtin_amdgcn_sched_barrier(0);
+    if (b >= nfull) {
+      const int kb = key_lo + b * kPrefillBlock;
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (kb + 32 * (kt >> 1) + 8 * q + 4 * (kt & 1) + r > it.pos0 + pl[u]) S[kt][u][r] = kNegInf;
+    }
+    float mx[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      mx[u] = kNegInf;
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx[u] = fmaxf(mx[u], S[kt][u][r]);
+      mx[u] *= sl2;
+    }
+    if (__any(mx[0] > m_run[0] + kSlack || mx[1] > m_run[1] + kSlack)) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        float m = fmaxf(mx[u], __shfl_xor(mx[u], 16));
+        m = fmaxf(m, __shfl_xor(m, 32));
+        const bool grow = m > m_run[u] + kSlack;
+        const float m_new = grow ? m : m_run[u];
+        const float alpha = grow ? fast_exp2(m_run[u] - m_new) : 1.f;
+        m_run[u] = m_new;
+        l_run[u] *= alpha;
+#pragma unroll
+        for (int ft = 0; ft < 8; ++ft) O[ft][u] *= alpha;
+      }
+    }
+    const float m_use[2] = {m_run[0] == kNegInf ? 0.f : m_run[0], m_run[1] == kNegInf ? 0.f : m_run[1]};
+    aim();
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {   // one transfer after each quarter of the exponentials
+      const int u = c & 1, s = c >> 1;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const f32x4& x = S[2 * s + (e >> 1)][u];
+        const uint32_t pr = pack_bf16x2(fast_exp2(x[2 * (e & 1)] * sl2 - m_use[u]),
+                                        fast_exp2(x[2 * (e & 1) + 1] * sl2 - m_use[u]));
+        pk[u][s][e] = pr;
+        l_run[u] = sum_bf16x2(pr, l_run[u]);
+      }
+      asm volatile("" : "+v"(pk[u][s]));   // computed here: sunk to its use, the transfers bunched up
+      __builtin_amdgcn_sched_barrier(0);
+      move(c);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto swap_halves = [] {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+  };
+
+  // vmcnt(n) of whole sets: all but the youngest n / 4 have landed
+  load_pids(0);
+  aim_k();
+  move(2);
+  move(3);
+  move_all();                                  // set -2: K of block 1, V of block 0
+  move_all();                                  // set -1
+  __builtin_amdgcn_s_waitcnt(0x0F70 | 8);      // K of block 0 has landed
+  swap_halves();
+  read_k_step(0);
+  read_k_step(1);
+  read_k_step(2);
+  if (late) {
+    move_all();                                // set 0
+    __builtin_amdgcn_s_waitcnt(0x0F70 | 8);
+    swap_halves();
+  }
+  for (int t = 0; t < nblk; ++t) {
+    if (t > 0)
+      matrix_part(true);
+    else
+      matrix_part(false);
+    if (!late) __builtin_amdgcn_s_waitcnt(0x0F70 | 4);
+    swap_halves();
+    vector_part(t);
+    if (late) __builtin_amdgcn_s_waitcnt(0x0F70 | 8);
+    swap_halves();
+  }
+  // PV of the last block; keys >= kend contribute zero V (their probabilities are
+  // already zero; this keeps unwritten slots out of the sum)
+  {
+    const int kb = key_lo + (nblk - 1) * kPrefillBlock;
+    const bool tail = kb + kPrefillBlock > kend;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int ft = 0; ft < 8; ++ft) {
+        u32x4 vf = read_v(s, ft);
+        if (tail) vf = keep_first(vf, 0, kend - (kb + 32 * s + 8 * q));
+        pv_step(s, ft, vf);
+      }
+  }
+  if (!late) swap_halves();
+  wait_vmem();   // no transfer outlives its buffers
+
+  // O^T register r of feature tile ft: feature 16 ft + 4 q + r of row tile u's row n.
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    float l = l_run[u] + __shfl_xor(l_run[u], 16);
+    l += __shfl_xor(l, 32);
+    if (!rvalid[u]) continue;
+    if (it.part < 0) {
+      const float inv = 1.f / l;
+      uint16_t* orow = a.out + (size_t(it.row0 + pl[u]) * a.hq + it.kvh * kGroup + (n & 7)) * kHeadDim + 4 * q;
+#pragma unroll
+      for (int ft = 0; ft < 8; ++ft) {
+        u32x2 v;
+        v[0] = pack_bf16x2(O[ft][u][0] * inv, O[ft][u][1] * inv);
+        v[1] = pack_bf16x2(O[ft][u][2] * inv, O[ft][u][3] * inv);
+        *reinterpret_cast<u32x2*>(orow + 16 * ft) = v;
+      }
+    } else {
+      const int slot = it.part + 32 * w + 16 * u + n;
+      float* acc = a.part_acc + size_t(slot) * kHeadDim + 4 * q;
+#pragma unroll
+      for (int ft = 0; ft < 8; ++ft) *reinterpret_cast<f32x4*>(acc + 16 * ft) = O[ft][u];
+      if (q == 0) a.part_ml[slot] = make_float2(m_run[u], l);
+    }
+  }
+#endif
 }
 
 // ---------------------------------------------------------------------------
@@ -660,12 +993,14 @@ __device__ __forceinline__ void decode_row(const StepArgs& a, const WorkItem& it
 
 template <int kW>
 __global__ __launch_bounds__(threads_of<kW>(), kW == 4 ? 2 : 1) void attn_step_kernel(StepArgs a) {
-  __shared__ __attribute__((aligned(1024))) char smem[4 * kBlockBytes];
+  __shared__ __attribute__((aligned(1024))) char smem[(kW == 8 ? 2 * kPPRing : 4) * kBlockBytes];
   const WorkItem it = a.items[blockIdx.x];
   if ((it.npos_kind >> 16) == kKindDecode)
     decode_row<kW>(a, it, smem);
+  else if constexpr (kW == 8)
+    prefill_pp(a, it, smem);
   else
-    prefill_tile<kW>(a, it, smem);
+    prefill_tile(a, it, smem);
 }
 
 // Merge split partials: for local row r of a combine item with partials

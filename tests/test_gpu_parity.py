@@ -194,6 +194,17 @@ def test_tp_shard_shape(lib, tile):
     compare(ds.out_f64(), oracle_out(data, ds.shape.scale), label=f"tp-shard/tile{tile}")
 
 
+@pytest.mark.parametrize("split", [0, 64, 192, 320])
+@pytest.mark.parametrize("n,cached", [(1 + 1, 62), (31, 161), (32, 224), (33, 319), (5, 4090), (40, 8250)])
+def test_large_tile_block_counts(lib, n, cached, split):
+    # 32-position tiles over one to 130 key blocks: fewer blocks than the LDS rings hold, every
+    # ring position at the end, page ids fetched again after 64 blocks, tiles with few rows and
+    # last pages with one key (the pool holds NaN wherever no key was written)
+    spec = I.StepSpec("blocks", [I.Seq(n, cached, 0), I.Seq(7, 9, 1)])
+    data, ds = run_step(lib, spec, 31, splits=(split, 0), tile=32, pool_fill=SENTINEL)
+    compare(ds.out_f64(), oracle_out(data, ds.shape.scale), label=f"blocks {n}@{cached} split={split}")
+
+
 @pytest.mark.parametrize("tile", [16, 32])
 def test_permuted_block_table_is_bit_identical(lib, tile):
     spec = I.random_small_step(3, max_seqs=6, max_n=70, max_c=300)
