@@ -410,8 +410,8 @@ __device__ __forceinline__ void prefill_tile(const StepArgs& a, const WorkItem& 
 // n = lane & 15), on 16x16x32 MFMAs, S^T = K Q^T and O^T += V^T P^T.
 //
 // What bounds it: per 64-key block a wave's MFMAs take 1,024 clocks of its SIMD, its
-// softmax about as many vector clocks, and the eight waves' operand reads 2,048
-// clocks of LDS at 128 B per clock, so the three have to overlap. Waves 0-3 and 4-7
+// softmax about as many vector clocks, and the eight waves read 256 KB of operands
+// from LDS, so the three have to overlap. Waves 0-3 and 4-7
 // (one of each per SIMD) therefore run half an iteration apart: while one half
 // issues the MFMAs of a block (QK^T of block t, PV of block t - 1), the other
 // exponentiates, and a workgroup barrier swaps them. K fragments are read during the
@@ -1008,8 +1008,45 @@ __global__ __launch_bounds__(threads_of<kW>(), kW == 4 ? 2 : 1) void attn_step_k
 // Block (item, y) handles rows 8y..8y+7 of the item; 32 lanes per row, 4
 // features per lane.
 constexpr int kCombineRowsPerBlock = 8;
-constexpr int kMergeBatch = 4;            // splits whose loads a merge thread issues together
 constexpr int kCombineThreads = 32 * kCombineRowsPerBlock;
+
+// Splits are merged in batches of kBatch whose (m, l) and accumulator loads are all
+// issued before any is used (one memory round trip per batch); a later batch rescales
+// what is merged so far to its larger maximum. Absent splits of a batch enter with
+// m = -inf and weigh 0. Every split gives each of its rows at least one key, so a real
+// split's m is finite.
+template <int kBatch>
+__device__ __forceinline__ void merge_splits(const float2* ml_row, const float* acc_row, int rows, int nsplit,
+                                             float& L, f32x4& acc) {
+  float M = kNegInf;
+  L = 0.f;
+  acc = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < nsplit; s0 += kBatch) {
+    float2 ml[kBatch];
+    f32x4 pa[kBatch];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const size_t at = size_t(min(s0 + i, nsplit - 1)) * rows;
+      ml[i] = ml_row[at];
+      pa[i] = *reinterpret_cast<const f32x4*>(acc_row + at * kHeadDim);
+      if (s0 + i >= nsplit) ml[i].x = kNegInf;
+    }
+    float Mb = M;
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) Mb = fmaxf(Mb, ml[i].x);
+    const float sc = fast_exp2(M - Mb);      // 0 while nothing is merged (M = -inf)
+    L *= sc;
+    acc *= sc;
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const float f = fast_exp2(ml[i].x - Mb);
+      L += f * ml[i].y;
+      acc += f * pa[i];
+    }
+    M = Mb;
+  }
+}
+
 __global__ __launch_bounds__(kCombineThreads) void combine_kernel(const CombineItem* items, const float2* part_ml,
                                                            const float* part_acc, uint16_t* out, int hq) {
   const CombineItem ci = items[blockIdx.x];
@@ -1017,37 +1054,17 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(const CombineI
   const int r = blockIdx.y * kCombineRowsPerBlock + (threadIdx.x >> 5);
   if (r >= rows) return;
   const int d0 = (threadIdx.x & 31) * 4;
-  // Splits are merged in batches of kMergeBatch whose (m, l) and accumulator loads
-  // are all issued before any is used (one memory round trip per batch); a later
-  // batch rescales what is merged so far to its larger maximum. Absent splits of a
-  // batch enter with m = -inf and weigh 0. Every split gives each of its rows at
-  // least one key, so a real split's m is finite.
-  float M = kNegInf, L = 0.f;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int s0 = 0; s0 < ci.nsplit; s0 += kMergeBatch) {
-    float2 ml[kMergeBatch];
-    f32x4 pa[kMergeBatch];
-#pragma unroll
-    for (int i = 0; i < kMergeBatch; ++i) {
-      const int slot = ci.part + min(s0 + i, ci.nsplit - 1) * rows + r;
-      ml[i] = part_ml[slot];
-      pa[i] = *reinterpret_cast<const f32x4*>(part_acc + size_t(slot) * kHeadDim + d0);
-      if (s0 + i >= ci.nsplit) ml[i].x = kNegInf;
-    }
-    float Mb = M;
-#pragma unroll
-    for (int i = 0; i < kMergeBatch; ++i) Mb = fmaxf(Mb, ml[i].x);
-    const float sc = fast_exp2(M - Mb);      // 0 while nothing is merged (M = -inf)
-    L *= sc;
-    acc *= sc;
-#pragma unroll
-    for (int i = 0; i < kMergeBatch; ++i) {
-      const float f = fast_exp2(ml[i].x - Mb);
-      L += f * ml[i].y;
-      acc += f * pa[i];
-    }
-    M = Mb;
-  }
+  const size_t slot = size_t(ci.part) + r;
+  const float2* ml_row = part_ml + slot;
+  const float* acc_row = part_acc + slot * kHeadDim + d0;
+  float L;
+  f32x4 acc;
+  // rows in many pieces (a few long decode rows) wait for a quarter of the round trips;
+  // the others don't load splits that are not there
+  if (ci.nsplit > 8)
+    merge_splits<16>(ml_row, acc_row, rows, ci.nsplit, L, acc);
+  else
+    merge_splits<4>(ml_row, acc_row, rows, ci.nsplit, L, acc);
   const float inv = 1.f / L;
   uint16_t* orow = out + (size_t(ci.row0 + r / kGroup) * hq + ci.kvh * kGroup + r % kGroup) * kHeadDim + d0;
   u32x2 v;

@@ -358,6 +358,22 @@ def test_decode_only_steps_take_even_pieces_about_one_per_cu(num_cus):
     assert ((fixed[:, 7] - fixed[:, 6]) <= 4096).all() and (fixed[:, 6] % 4096 == 0).all()
 
 
+@pytest.mark.parametrize("rows,keys", [(1, 1), (1, 768), (8, 500), (1, 769), (3, 5000), (1, 30000), (2, 200000)])
+def test_few_decode_rows_are_not_cut_finer_than_the_merge_is_worth(rows, keys):
+    """Decode rows of up to 768 keys stay whole; longer ones take pieces of about
+    sqrt(32 keys) keys or more, and no piece exceeds one item's page-id capacity."""
+    spec = I.StepSpec("few", [I.Seq(1, keys - 1, i) for i in range(rows)])
+    items = ppas.plan_items(shape(), spec.descriptors(), num_cus=256)
+    pieces = len(items) // (2 * rows)
+    assert len(items) == 2 * rows * pieces
+    if keys <= 768:
+        assert pieces == 1
+    else:
+        assert 1 < pieces <= max((keys / 32) ** 0.5 + 0.5, -(-keys // (16384 - 32))), pieces
+    assert (items[:, 7] - items[:, 6]).max() <= 16384
+    check_coverage(spec, items)
+
+
 def test_binding_fails_loudly_without_the_library(tmp_path):
     """No fallback: a copy of the package without libppas.so refuses to import its
     binding (and the device-step module built on it)."""

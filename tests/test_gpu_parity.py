@@ -205,6 +205,14 @@ def test_large_tile_block_counts(lib, n, cached, split):
     compare(ds.out_f64(), oracle_out(data, ds.shape.scale), label=f"blocks {n}@{cached} split={split}")
 
 
+@pytest.mark.parametrize("pieces", [2, 4, 5, 8, 9, 16, 17, 33, 96])
+def test_merge_batches(lib, pieces):
+    # one decode row in `pieces` pieces of 32 keys, the last one ragged, beside a row in half as many
+    spec = I.StepSpec("pieces", [I.Seq(1, 32 * pieces - 9, 0), I.Seq(1, 16 * pieces, 1)])
+    data, ds = run_step(lib, spec, 32, splits=(0, 32))
+    compare(ds.out_f64(), oracle_out(data, ds.shape.scale), label=f"merge of {pieces}")
+
+
 @pytest.mark.parametrize("tile", [16, 32])
 def test_permuted_block_table_is_bit_identical(lib, tile):
     spec = I.random_small_step(3, max_seqs=6, max_n=70, max_c=300)
