@@ -422,7 +422,7 @@ __device__ __forceinline__ void prefill_tile(const StepArgs& a, const WorkItem& 
 // run, as vector and matrix instructions share the SIMD's issue), and the chip clocks
 // at 2.1 GHz under this load.
 //
-// Measured on one 16,384-position chunk behind 8,616 cached ones, 32/4 heads: 1,816 us
+// Measured on one 16,384-position chunk behind 8,616 cached ones, 16/2 heads: 1,816 us
 // against 1,962 us for the same tile with all waves in step (which left the overlap to
 // chance). Also measured: reading V and K in the matrix half only, 2,000 us; 32x32x16
 // MFMAs on this schedule, 1,990 us.
