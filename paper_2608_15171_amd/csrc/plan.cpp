@@ -20,7 +20,6 @@ constexpr double kInterleaveRatio = PPAS_INTERLEAVE_RATIO;
 #ifndef PPAS_LARGE_TILE_DECODE_SHARE
 #define PPAS_LARGE_TILE_DECODE_SHARE 0.05
 #endif
-constexpr int64_t kDecodeWhole = 768;   // decode-only steps of rows up to this many keys don't cut them
 constexpr double kLargeTileDecodeShare = PPAS_LARGE_TILE_DECODE_SHARE;
 // when interleaving, prefill advances at this multiple of the decode fraction
 #ifndef PPAS_INTERLEAVE_BIAS
@@ -122,13 +121,12 @@ void make_plan(const ppas_shape& shape, const ppas_seq* seqs, int32_t n_seqs, in
     }
     return keys * hkv;
   };
-  int64_t decode_keys = 0, longest_decode = 0, large_tiles = 0;
+  int64_t decode_keys = 0, large_tiles = 0;
   for (int32_t s = 0; s < n_seqs; ++s) {
     const ppas_seq& q = seqs[s];
-    if (q.n_query == 1) {
+    if (q.n_query == 1)
       decode_keys += int64_t(q.cached_len + 1) * hkv;
-      longest_decode = std::max<int64_t>(longest_decode, int64_t(q.cached_len) + 1);
-    } else
+    else
       large_tiles += ceil_div(q.n_query, kTilePosLarge) * hkv;
   }
 
@@ -182,21 +180,18 @@ void make_plan(const ppas_shape& shape, const ppas_seq* seqs, int32_t n_seqs, in
   // 205 us with about two per CU, ragged). A piece never exceeds the page-id
   // capacity of a decode item.
   //
-  // A few rows would be cut too fine that way. An item of k keys takes about 6 ns per
-  // key, and every piece of a row about 0.12 us of its merge, so sqrt(20 kend) keys per
-  // piece balance the two; 32 for 20 favours the fewer partials (one row of 3,071 keys:
-  // 30.3 us in 96 pieces per KV head, 12 us in 10; of 30,000: 30.8 us in 128, 22.6 us in
-  // 30). Where no row is longer than kDecodeWhole keys none is cut and the merge launch
-  // is saved: 8 rows of 500 keys 8.2 us against 10.5, one of 600 8.4 against 13.6; at
-  // 1,200 keys the pieces win, 10.1 against 11.6.
+  // Fewer, longer pieces in a step of a few rows would shorten the merge (11.7 us after
+  // 5.4 us of attention for one row of 3,071 keys in 96 pieces per KV head), but cost
+  // precision: probabilities are rounded to bf16 relative to the largest of their piece,
+  // which is then exactly 1, so fewer pieces leave more of the large probabilities
+  // rounded. Against 64 bits that row's error would go from 2.12e-3 to 2.31e-3 in ten
+  // pieces, that of 500 keys left whole from 2.01e-3 to 2.25e-3.
   const bool decode_even = prefill_keys == 0 && decode_keys > 0 && opts.decode_split <= 0;
-  const bool decode_whole = decode_even && longest_decode <= kDecodeWhole;
   auto piece_bounds = [&](int64_t kend, int64_t pos0, int kind) {
     std::vector<int64_t> b{0};
     if (kind == kKindDecode && decode_even) {
-      const int64_t fine = std::min((kend * num_cus + decode_keys / 2) / decode_keys,
-                                    int64_t(std::sqrt(double(kend) / 32.0) + 0.5));
-      const int64_t n = decode_whole ? 1 : std::max(ceil_div(kend, int64_t(kDecodeMaxKeys - kDecodeBlock)), fine);
+      const int64_t n = std::max<int64_t>(ceil_div(kend, int64_t(kDecodeMaxKeys - kDecodeBlock)),
+                                          (kend * num_cus + decode_keys / 2) / decode_keys);
       for (int64_t k = 1; k < n; ++k) b.push_back(kend * k / n / kDecodeBlock * kDecodeBlock);
     } else if (kind == kKindDecode) {
       for (int64_t k = 1; k * ksd < kend; ++k) b.push_back(k * ksd);
