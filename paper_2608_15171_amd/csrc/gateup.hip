@@ -405,8 +405,10 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& a, char* smem, int m_f
   // memory slots read X 0; X 1; W 1; W 0 of the next stage, and issue W 1 of the
   // stage after next; then W 0, X 0, X 1 of the one after that: each unit two
   // phases after its buffer was last read, and five units behind the one the next
-  // phase needs. BM < 256, phases W 0 and W 1: the slots read X and W 0; W 1, and
-  // issue X and W 0, then W 1, two stages ahead of the reads.
+  // phase needs. A phase's MFMAs wait for what its memory slot read, except W 0, which
+  // the next stage uses first: the last phase waits for it by itself. BM < 256, phases
+  // W 0 and W 1: the slots read X and W 0; W 1, and issue X and W 0, then W 1, two
+  // stages ahead of the reads.
   auto stage = [&](bool first) {
     if constexpr (BM == 256) {
       constexpr int kWaitA = 3 * C::kDX + 2 * C::kDW, kWaitB = 2 * C::kDX + 3 * C::kDW;
@@ -439,6 +441,10 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& a, char* smem, int m_f
       wait_vmcnt<kWaitA>();
       bare_barrier();
       mma(1, 0, first);
+      // these MFMAs don't use the W 0 just read: it is waited for here, a barrier before
+      // the other half may refill its buffer
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(0xC07F);
     } else {
       issue_x(0);
       issue_w(0);
@@ -574,6 +580,7 @@ __device__ __forceinline__ void run_tiles(const GemmArgs& a, char* smem, int m_f
             S::out(eb, lane, a.y, it.m0 + g * C::HM + wm * QM + 16 * tb,
                    (kAct ? it.n0 / 2 : it.n0 + h * kHN) + wn * QN, a.T, ncols);
           }
+      __builtin_amdgcn_s_waitcnt(0xC07F);   // the reads of rows past the edge, which no store waits for
     }
     bare_barrier();
   }
