@@ -369,6 +369,18 @@ ppas_status ppas_gateup_act(const void* x, const void* w, void* y, int32_t n_tok
 size_t ppas_gateup_act_workspace_bytes(int32_t n_tokens, int32_t hidden, int32_t n_inter);
 
 /*
+ * Kernel choice of a projection call, for tests (host only, no HIP call): the
+ * kernel that ppas_gateup_proj, or with `activation` ppas_gateup_act (n_out = 2
+ * n_inter), takes for this shape and workspace size on a device of num_cus compute
+ * units (0 = 256), `aligned` if x and w are. Writes 7 int32 to `choice`: kernel (0
+ * tiles, 1 few rows, 2 general), token rows of a main tile or few-row workgroup,
+ * main tiles and 64-row tiles along the tokens, weight-row tiles of a few-row
+ * workgroup and their rows, reduction splits. PPAS_EINVAL for n_tokens == 0.
+ */
+ppas_status ppas_gateup_choice(int32_t n_tokens, int32_t hidden, int32_t n_out, int32_t activation,
+                               int32_t aligned, size_t workspace_bytes, int32_t num_cus, int32_t* choice);
+
+/*
  * A plain streaming read of `bytes` bytes of device memory at `buf`: the
  * device's attainable HBM read rate, the measured ceiling beside the spec peak
  * for the memory-bound kernels above (the library's own measurement aid, not a

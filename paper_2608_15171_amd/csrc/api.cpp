@@ -495,6 +495,14 @@ size_t ppas_gateup_workspace_bytes(int32_t n_tokens, int32_t hidden, int32_t n_o
 
 namespace {
 
+// The most splits of a call: the automatic number, reduced to what the workspace
+// holds (no split needs none).
+int allowed_splits(int32_t n_tokens, int32_t hidden, int32_t n_out, size_t workspace_bytes, int cus) {
+  int splits = gateup_splits(n_tokens, hidden, n_out, cus);
+  while (splits > 1 && gateup_workspace_bytes(n_tokens, n_out, splits) > workspace_bytes) --splits;
+  return gateup_tiles(n_tokens, n_out) * splits > INT32_MAX ? 1 : splits;
+}
+
 // Both projection entry points: n_out weight rows; with `act` the output holds the
 // gated activation of the two halves (n_out / 2 columns).
 ppas_status gateup_call(const void* x, const void* w, void* y, int32_t n_tokens, int32_t hidden, int32_t n_out,
@@ -508,10 +516,7 @@ ppas_status gateup_call(const void* x, const void* w, void* y, int32_t n_tokens,
   if (!x || !w || !y || (workspace_bytes > 0 && !workspace)) return PPAS_EINVAL;
   const DeviceInfo dev = current_device();
   if (!dev.gfx950) return PPAS_EUNSUPPORTED;
-  // the automatic split, reduced to what the workspace holds (no split needs none)
-  int splits = gateup_splits(n_tokens, hidden, n_out, dev.cus);
-  while (splits > 1 && gateup_workspace_bytes(n_tokens, n_out, splits) > workspace_bytes) --splits;
-  if (gateup_tiles(n_tokens, n_out) * splits > INT32_MAX) splits = 1;
+  const int splits = allowed_splits(n_tokens, hidden, n_out, workspace_bytes, dev.cus);
   const hipError_t e = launch_gateup(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w),
                                      static_cast<uint16_t*>(y), n_tokens, hidden, n_out, act, splits,
                                      static_cast<float*>(workspace), dev.cus, static_cast<hipStream_t>(hip_stream),
@@ -548,6 +553,19 @@ ppas_status ppas_gateup_act(const void* x, const void* w, void* y, int32_t n_tok
   } catch (...) {
     return PPAS_EINVAL;
   }
+}
+
+ppas_status ppas_gateup_choice(int32_t n_tokens, int32_t hidden, int32_t n_out, int32_t activation, int32_t aligned,
+                               size_t workspace_bytes, int32_t num_cus, int32_t* choice) {
+  const ppas_status st = check_gateup(n_tokens, hidden, n_out);
+  if (st != PPAS_OK) return st;
+  if (!choice || n_tokens == 0 || num_cus < 0 || (activation && n_out % 2 != 0)) return PPAS_EINVAL;
+  const int cus = num_cus > 0 ? num_cus : 256;
+  const GateupChoice c = gateup_choose(n_tokens, hidden, n_out, activation != 0, aligned != 0,
+                                       allowed_splits(n_tokens, hidden, n_out, workspace_bytes, cus), cus);
+  const int32_t v[7] = {c.kernel, c.rows, c.main_m, c.tail_m, c.g, c.wr, c.splits};
+  std::copy(v, v + 7, choice);
+  return PPAS_OK;
 }
 
 ppas_status ppas_stream_read(const void* buf, size_t bytes, void* sink, const ppas_events* events,

@@ -33,7 +33,18 @@ hipError_t launch_attn_step(const uint16_t* q, uint16_t* out, const uint16_t* kp
 // (N2 even, y [T][N2/2]). The reduction is split over at most max_splits
 // workgroups per output tile, as many as pay, whose fp32 partial sums
 // (gateup_workspace_bytes of `part`, columns in weight-row order) a second launch
-// adds in order. `cus` is the device's compute-unit count.
+// adds in order. `cus` is the device's compute-unit count. gateup_choose (host
+// only) is the kernel that such a call takes; `aligned`: x and w on 16 bytes.
+struct GateupChoice {
+  enum Kernel { kTiles = 0, kRows = 1, kGeneral = 2 };
+  Kernel kernel = kGeneral;
+  int32_t rows = 256;                       // token rows of a main tile, or of a few-row workgroup
+  int32_t g = 0, wr = 0;                    // few rows: weight-row tiles per workgroup and their rows
+  int32_t splits = 1;
+  int32_t main_m = 0, tail_m = 0;           // tiles: main ones along the token rows, 64-row ones after them
+  int32_t light = 0, grid = 0, block = 8;   // tiles: see GemmArgs
+};
+GateupChoice gateup_choose(int32_t T, int32_t H, int32_t N2, bool act, bool aligned, int max_splits, int cus);
 hipError_t launch_gateup(const uint16_t* x, const uint16_t* w, uint16_t* y, int32_t T, int32_t H, int32_t N2,
                          bool act, int max_splits, float* part, int cus, hipStream_t stream, hipEvent_t ev_start,
                          hipEvent_t ev_stop);

@@ -782,10 +782,13 @@ __global__ __launch_bounds__(64 * kRowsWaves, 1) void gateup_rows_kernel(GemmArg
 #endif
 }
 
+// Token rows per workgroup.
+int rows_tokens(int32_t T) { return T <= 16 ? 16 : T <= 32 ? 32 : 64; }
+
 template <int G, int WR, bool kAct>
 void launch_rows(const GemmArgs& a, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
   const int ncols = kAct ? a.I : a.N2, per = (kAct ? WR / 2 : WR) * G;
-  const int xt = a.T <= 16 ? 1 : a.T <= 32 ? 2 : 4;
+  const int xt = rows_tokens(a.T) / 16;
   const dim3 grid(unsigned((ncols + per - 1) / per), unsigned((a.T + 16 * xt - 1) / (16 * xt))), block(64 * kRowsWaves);
   if (xt == 1)
     hipExtLaunchKernelGGL((gateup_rows_kernel<1, G, WR, kAct>), grid, block, 0, stream, ev_start, ev_stop, 0, a);
@@ -917,7 +920,7 @@ constexpr int kRowsMaxT = 256;   // measured up to here; from about 64 rows the 
 // projections; 13 % rms), over which the choice is 0.7 % slower than the best.
 constexpr double kTilesBase = 7.5;
 double rows_cost(int32_t T, int32_t H, int32_t N2, int cus, const RowsShape& v) {
-  const int xt = T <= 16 ? 1 : T <= 32 ? 2 : 4;
+  const int xt = rows_tokens(T) / 16;
   const double cols = double((int64_t(N2) + v.g * v.wr - 1) / (v.g * v.wr));
   const double mt = (T + 16 * xt - 1) / (16 * xt);
   const int slot = (v.g * v.wr + 16 * xt) * kRow;
@@ -947,37 +950,68 @@ size_t gateup_workspace_bytes(int32_t T, int32_t N2, int splits) {
   return splits > 1 ? size_t(splits) * size_t(T) * size_t(N2) * sizeof(float) : 0;
 }
 
+GateupChoice gateup_choose(int32_t T, int32_t H, int32_t N2, bool act, bool aligned, int max_splits, int cus) {
+  GateupChoice r;
+  r.splits = max_splits;
+  // The transfers need 16-byte aligned rows and 32-bit offsets within a unit.
+  if (!aligned || int64_t(H) * 2 >= kMaxPitch) return r;
+  // one workgroup per compute unit (a multiple of 8, so that each stays on one XCD's
+  // share of the tiles)
+  const int grid_max = std::max(8, cus / 8 * 8);
+  // Narrow outputs (the K and V projections, whose results are cached) are summed
+  // in 256-feature blocks added in order, whatever the tiles: by blocks of four
+  // stages, or by the full split into such blocks. The result then does not depend
+  // on the number of tokens beside it. Wider outputs take the cheapest split.
+  const bool narrow = !act && N2 <= 2 * kBN;
+  const int full = gateup_splits(T, H, N2, cus);
+  Shape best;
+  for (int bm : {256, 128, 64})
+    for (int s = 1; s <= max_splits; ++s) {
+      if (narrow && ((s > 1 && s != full) || (bm == 256 && T >= 256))) continue;
+      const Shape c = shape_cost(T, H, N2, grid_max, bm, s);
+      if (c.items > INT32_MAX / 2) continue;
+      if (best.bm == 0 || c.cost < best.cost) best = c;
+    }
+  if (best.bm == 0) return r;
+  r.kernel = GateupChoice::kTiles;
+  r.rows = best.bm;
+  r.splits = best.splits;
+  r.main_m = best.main_m;
+  r.tail_m = best.tail_m;
+  r.light = best.light;
+  r.grid = int32_t(std::min<int64_t>(best.items, grid_max));
+  r.block = narrow ? 4 : 8;
+  if (T > kRowsMaxT) return r;
+  double cost = best.cost + kTilesBase;
+  for (const RowsShape& v : kRowsShapes) {
+    if (!(act ? v.with_act : v.without) || N2 / (v.g * v.wr) >= (1 << 22) || (narrow && v.g > 1)) continue;
+    const double c = rows_cost(T, H, N2, grid_max, v);
+    if (c < cost) {
+      cost = c;
+      r.kernel = GateupChoice::kRows;
+      r.rows = rows_tokens(T);
+      r.splits = 1;
+      r.g = v.g;
+      r.wr = v.wr;
+    }
+  }
+  return r;
+}
+
 hipError_t launch_gateup(const uint16_t* x, const uint16_t* w, uint16_t* y, int32_t T, int32_t H, int32_t N2,
                          bool act, int max_splits, float* part, int cus, hipStream_t stream, hipEvent_t ev_start,
                          hipEvent_t ev_stop) {
   if (T <= 0) return hipSuccess;
   if (max_splits < 1 || max_splits > H / kBK || (max_splits > 1 && !part) || (act && N2 % 2 != 0))
     return hipErrorInvalidValue;
-  int splits = max_splits;
+  const bool aligned = reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(w) % 16 == 0;
+  const GateupChoice c = gateup_choose(T, H, N2, act, aligned, max_splits, cus);
+  const int splits = c.splits;
+  hipEvent_t ev = splits > 1 ? nullptr : ev_stop;
   hipError_t e;
-  // The transfers need 16-byte aligned rows and 32-bit offsets within a unit.
-  const bool regular = reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(w) % 16 == 0 &&
-                       int64_t(H) * 2 < kMaxPitch;
-  if (regular) {
-    // one workgroup per compute unit (a multiple of 8, so that each stays on one XCD's
-    // share of the tiles)
-    const int grid_max = std::max(8, cus / 8 * 8);
-    // Narrow outputs (the K and V projections, whose results are cached) are summed
-    // in 256-feature blocks added in order, whatever the tiles: by blocks of four
-    // stages, or by the full split into such blocks. The result then does not depend
-    // on the number of tokens beside it. Wider outputs take the cheapest split.
-    const bool narrow = !act && N2 <= 2 * kBN;
-    const int full = gateup_splits(T, H, N2, cus);
-    Shape best;
-    for (int bm : {256, 128, 64})
-      for (int s = 1; s <= max_splits; ++s) {
-        if (narrow && ((s > 1 && s != full) || (bm == 256 && T >= 256))) continue;
-        const Shape c = shape_cost(T, H, N2, grid_max, bm, s);
-        if (c.items > INT32_MAX / 2) continue;
-        if (best.bm == 0 || c.cost < best.cost) best = c;
-      }
-    if (best.bm == 0) return hipErrorInvalidValue;
-    splits = best.splits;
+  if (c.kernel == GateupChoice::kGeneral) {
+    e = launch_gateup_any(x, w, y, T, H, N2, act, splits, part, cus, stream, ev_start, ev);
+  } else {
     GemmArgs a;
     a.x = x;
     a.w = w;
@@ -989,64 +1023,40 @@ hipError_t launch_gateup(const uint16_t* x, const uint16_t* w, uint16_t* y, int3
     a.I = N2 / 2;
     // with the activation a tile holds 128 features and their two weight rows each
     a.tiles_n = (N2 + kBN - 1) / kBN;
-    a.main_m = best.main_m;
-    a.tail_m = best.tail_m;
+    a.main_m = c.main_m;
+    a.tail_m = c.tail_m;
     a.splits = splits;
-    a.light = best.light;
-    a.block = narrow ? 4 : 8;
-    if (T <= kRowsMaxT) {
-      const RowsShape* rows = nullptr;
-      double cost = best.cost + kTilesBase;
-      for (const RowsShape& v : kRowsShapes) {
-        if (!(act ? v.with_act : v.without) || N2 / (v.g * v.wr) >= (1 << 22) || (narrow && v.g > 1)) continue;
-        const double c = rows_cost(T, H, N2, grid_max, v);
-        if (c < cost) {
-          cost = c;
-          rows = &v;
-        }
+    a.light = c.light;
+    a.block = c.block;
+    if (c.kernel == GateupChoice::kRows) {
+      const int shape = 100 * int(act) + 10 * c.g + (c.wr == 16);
+      switch (shape) {
+        case 10: launch_rows<1, 8, false>(a, stream, ev_start, ev); break;
+        case 11: launch_rows<1, 16, false>(a, stream, ev_start, ev); break;
+        case 21: launch_rows<2, 16, false>(a, stream, ev_start, ev); break;
+        case 41: launch_rows<4, 16, false>(a, stream, ev_start, ev); break;
+        case 61: launch_rows<6, 16, false>(a, stream, ev_start, ev); break;
+        case 120: launch_rows<2, 8, true>(a, stream, ev_start, ev); break;
+        case 121: launch_rows<2, 16, true>(a, stream, ev_start, ev); break;
+        case 141: launch_rows<4, 16, true>(a, stream, ev_start, ev); break;
+        case 161: launch_rows<6, 16, true>(a, stream, ev_start, ev); break;
+        default: return hipErrorInvalidValue;
       }
-      if (rows) {
-        if (act) {
-          if (rows->wr == 8)
-            launch_rows<2, 8, true>(a, stream, ev_start, ev_stop);
-          else if (rows->g == 2)
-            launch_rows<2, 16, true>(a, stream, ev_start, ev_stop);
-          else if (rows->g == 4)
-            launch_rows<4, 16, true>(a, stream, ev_start, ev_stop);
-          else
-            launch_rows<6, 16, true>(a, stream, ev_start, ev_stop);
-        } else {
-          if (rows->wr == 8)
-            launch_rows<1, 8, false>(a, stream, ev_start, ev_stop);
-          else if (rows->g == 1)
-            launch_rows<1, 16, false>(a, stream, ev_start, ev_stop);
-          else if (rows->g == 2)
-            launch_rows<2, 16, false>(a, stream, ev_start, ev_stop);
-          else if (rows->g == 4)
-            launch_rows<4, 16, false>(a, stream, ev_start, ev_stop);
-          else
-            launch_rows<6, 16, false>(a, stream, ev_start, ev_stop);
-        }
-        return hipGetLastError();
-      }
-    }
-    const dim3 grid(unsigned(std::min<int64_t>(best.items, grid_max)));
-    hipEvent_t ev = splits > 1 ? nullptr : ev_stop;
-    if (best.bm == 256) {
-      if (act)
-        hipExtLaunchKernelGGL((gateup_kernel<256, true>), grid, dim3(kThreads), 0, stream, ev_start, ev, 0, a);
-      else
-        hipExtLaunchKernelGGL((gateup_kernel<256, false>), grid, dim3(kThreads), 0, stream, ev_start, ev, 0, a);
     } else {
-      if (act)
-        hipExtLaunchKernelGGL((gateup_kernel<128, true>), grid, dim3(kThreads), 0, stream, ev_start, ev, 0, a);
-      else
-        hipExtLaunchKernelGGL((gateup_kernel<128, false>), grid, dim3(kThreads), 0, stream, ev_start, ev, 0, a);
+      const dim3 grid{unsigned(c.grid)};
+      if (c.rows == 256) {
+        if (act)
+          hipExtLaunchKernelGGL((gateup_kernel<256, true>), grid, dim3(kThreads), 0, stream, ev_start, ev, 0, a);
+        else
+          hipExtLaunchKernelGGL((gateup_kernel<256, false>), grid, dim3(kThreads), 0, stream, ev_start, ev, 0, a);
+      } else {
+        if (act)
+          hipExtLaunchKernelGGL((gateup_kernel<128, true>), grid, dim3(kThreads), 0, stream, ev_start, ev, 0, a);
+        else
+          hipExtLaunchKernelGGL((gateup_kernel<128, false>), grid, dim3(kThreads), 0, stream, ev_start, ev, 0, a);
+      }
     }
     e = hipGetLastError();
-  } else {
-    e = launch_gateup_any(x, w, y, T, H, N2, act, splits, part, cus, stream, ev_start,
-                          splits > 1 ? nullptr : ev_stop);
   }
   if (e != hipSuccess || splits == 1) return e;
   const int64_t total = act ? int64_t(T) * (N2 / 2) : int64_t(T) * N2;

@@ -99,6 +99,8 @@ _lib.ppas_gateup_act.restype = ctypes.c_int
 _lib.ppas_gateup_act.argtypes = [_vp, _vp, _vp, _i32, _i32, _i32, _vp, _sz, _E, _vp]
 _lib.ppas_gateup_act_workspace_bytes.restype = _sz
 _lib.ppas_gateup_act_workspace_bytes.argtypes = [_i32, _i32, _i32]
+_lib.ppas_gateup_choice.restype = ctypes.c_int
+_lib.ppas_gateup_choice.argtypes = [_i32, _i32, _i32, _i32, _i32, _sz, _i32, _vp]
 _lib.ppas_stream_read.restype = ctypes.c_int
 _lib.ppas_stream_read.argtypes = [_vp, _sz, _vp, _E, _vp]
 _lib.ppas_plan_items.restype = _i32
@@ -293,6 +295,19 @@ def gateup_proj(x, w, y, workspace=None, events: Events | None = None, stream=No
     st = _lib.ppas_gateup_proj(_dev(x, "x"), _dev(w, "w"), _dev(y, "y"), T, H, N, _dev(workspace, "workspace"),
                                ws_bytes, None if events is None else ctypes.byref(events), _stream(stream))
     _check(st, "ppas_gateup_proj")
+
+
+def gateup_choice(n_tokens: int, hidden: int, n_out: int, activation: bool = False, aligned: bool = True,
+                  workspace_bytes: int | None = None, num_cus: int = 0) -> dict:
+    """The kernel a projection call takes (host only, for tests); workspace_bytes: None = as many as it can use."""
+    out = np.zeros(7, dtype=np.int32)
+    nbytes = (1 << 62) if workspace_bytes is None else int(workspace_bytes)
+    _check(_lib.ppas_gateup_choice(int(n_tokens), int(hidden), int(n_out), int(activation), int(aligned), nbytes,
+                                   int(num_cus), _host_ptr(out)), "ppas_gateup_choice")
+    names = ("kernel", "rows", "main_tiles", "small_tiles", "weight_tiles", "weight_rows", "splits")
+    c = dict(zip(names, out.tolist()))
+    c["kernel"] = ("tiles", "rows", "general")[c["kernel"]]
+    return c
 
 
 def gateup_act_workspace_bytes(n_tokens: int, hidden: int, n_inter: int) -> int:

@@ -358,6 +358,32 @@ def test_decode_only_steps_take_even_pieces_about_one_per_cu(num_cus):
     assert ((fixed[:, 7] - fixed[:, 6]) <= 4096).all() and (fixed[:, 6] % 4096 == 0).all()
 
 
+def test_gateup_choice_query():
+    """The host-only query of a call's kernel: bad sizes refused as by the calls themselves,
+    the general kernel for what the others cannot take, splits within the workspace."""
+    C = ppas.gateup_choice
+    for bad, st in (((0, 64, 8), ppas.PPAS_EINVAL), ((8, 100, 8), ppas.PPAS_EUNSUPPORTED), ((8, 0, 8), ppas.PPAS_EINVAL),
+                    ((8, 64, -1), ppas.PPAS_EINVAL), ((8, 64, 2 ** 31 - 512), ppas.PPAS_ERANGE)):
+        with pytest.raises(ppas.PPASError) as ex:
+            C(*bad)
+        assert ex.value.status == st, bad
+    with pytest.raises(ppas.PPASError):
+        C(8, 64, 7, activation=True)
+    assert C(24, 2048, 4096, aligned=False)["kernel"] == "general"
+    assert C(24, 2 ** 23, 4096)["kernel"] == "general" and C(24, 2 ** 23 - 64, 4096)["kernel"] != "general"
+    for T in (1, 20, 64, 257, 700, 2056, 16384):
+        for H, N in ((2048, 22016), (11008, 2048), (2048, 256), (64, 40)):
+            need = ppas.gateup_workspace_bytes(T, H, N)
+            most = max(1, need // (4 * T * N))
+            for aligned in (True, False):
+                full, none = C(T, H, N, aligned=aligned), C(T, H, N, aligned=aligned, workspace_bytes=0)
+                assert none["splits"] == 1 and 1 <= full["splits"] <= most, (T, H, N)
+                assert aligned or full["splits"] == most
+                if full["kernel"] == "tiles":
+                    assert full["main_tiles"] * full["rows"] + 64 * full["small_tiles"] >= T
+                    assert full["main_tiles"] * full["rows"] + 64 * (full["small_tiles"] - 1) < T
+
+
 @pytest.mark.parametrize("rows,keys", [(1, 1), (1, 600), (8, 500), (1, 3072), (3, 5000), (1, 30000), (2, 200000)])
 def test_few_decode_rows_are_cut_as_finely_as_many(rows, keys):
     """A few decode rows take about one piece per compute unit like any decode-only step, down
