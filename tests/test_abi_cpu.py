@@ -384,6 +384,23 @@ def test_gateup_choice_query():
                     assert full["main_tiles"] * full["rows"] + 64 * (full["small_tiles"] - 1) < T
 
 
+@pytest.mark.parametrize("num_cus", [256, 304, 64])
+def test_narrow_projections_split_into_whole_blocks(num_cus):
+    """Up to 512 columns over a hidden size of one to eight 256-feature blocks: no split, or one
+    into exactly these blocks, so that the order of the sums is that of the hidden size alone.
+    Longer ones are free to take any split and tile."""
+    tokens = [*range(1, 520, 3), *range(520, 12000, 53)]
+    for H in (256, 512, 1024, 1792, 2048):
+        for N in (40, 128, 256, 512):
+            for T in tokens:
+                c = ppas.gateup_choice(T, H, N, num_cus=num_cus)
+                assert c["splits"] in (1, H // 256), (T, H, N, c)
+                assert c["kernel"] == "rows" and c["weight_tiles"] == 1 or \
+                    c["kernel"] == "tiles" and (c["rows"] < 256 or c["main_tiles"] == 0), (T, H, N, c)
+    others = [ppas.gateup_choice(T, H, N, num_cus=num_cus) for H, N in ((4096, 512), (3264, 128)) for T in tokens]
+    assert len({c["splits"] for c in others}) > 4
+
+
 @pytest.mark.parametrize("rows,keys", [(1, 1), (1, 600), (8, 500), (1, 3072), (3, 5000), (1, 30000), (2, 200000)])
 def test_few_decode_rows_are_cut_as_finely_as_many(rows, keys):
     """A few decode rows take about one piece per compute unit like any decode-only step, down

@@ -169,12 +169,14 @@ def test_few_rows_every_element(lib, T, H, N):
     check(f64(lib, run(lib, xb, wb)), xb, wb, label=f"T{T} H{H} N{N}")
 
 
-def test_narrow_output_does_not_depend_on_the_rows_beside_it(lib):
-    """The K and V projections (up to 512 columns) add the same 256-feature block sums in
-    the same order in every kernel: a row's bits are the same in calls of any size."""
+@pytest.mark.parametrize("H,N", [(2048, 256), (2048, 512), (1024, 500), (256, 128)])
+def test_narrow_output_does_not_depend_on_the_rows_beside_it(lib, H, N):
+    """The K and V projections (up to 512 columns over one to eight 256-feature blocks) add the
+    same block sums in the same order in every kernel: a row's bits are the same in calls of
+    any size."""
     ppas, step, torch = lib
-    wb = I.gateup_weight(10, hidden=2048, inter=128)
-    xb = I.gateup_tokens(10, 2500, 0, hidden=2048)
+    wb = I.gateup_weight(10, hidden=H, inter=N // 2)
+    xb = I.gateup_tokens(10, 2500, 0, hidden=H)
     whole = run(lib, xb, wb)
     for n in (1, 16, 40, 200, 256, 300, 700, 1100):
         part = run(lib, xb[:n], wb)
