@@ -563,8 +563,8 @@ ppas_status ppas_gateup_choice(int32_t n_tokens, int32_t hidden, int32_t n_out, 
   const int cus = num_cus > 0 ? num_cus : 256;
   const GateupChoice c = gateup_choose(n_tokens, hidden, n_out, activation != 0, aligned != 0,
                                        allowed_splits(n_tokens, hidden, n_out, workspace_bytes, cus), cus);
-  const int32_t v[7] = {c.kernel, c.rows, c.main_m, c.tail_m, c.g, c.wr, c.splits};
-  std::copy(v, v + 7, choice);
+  const int32_t v[8] = {c.kernel, c.rows, c.main_m, c.tail_m, c.g, c.wr, c.splits, c.block};
+  std::copy(v, v + 8, choice);
   return PPAS_OK;
 }
 

@@ -85,7 +85,7 @@ struct GemmArgs {
   int32_t tail_m;         // 64-row tiles of the rows after them
   int32_t splits;         // reduction split over this many workgroups per tile
   int32_t light;          // small tiles a workgroup with one main tile fewer takes first
-  int32_t block;          // stages per block of a two-level sum (tiles below 256 rows, few-row calls)
+  int32_t block;          // stages per block of a two-level sum (tiles below 256 rows, few-row calls): 4 or 8
 };
 
 __device__ __forceinline__ u32x4 lds16(const char* p) { return *reinterpret_cast<const u32x4*>(p); }
@@ -680,7 +680,7 @@ __global__ __launch_bounds__(64 * kRowsWaves, 1) void gateup_rows_kernel(GemmArg
 
   // Two-level sums, as in the tile kernels. In order: blocks of four chunks, wave w
   // taking blocks w, w + NW, ...; otherwise blocks of eight of the wave's chunks
-  // w, w + NW, ...
+  // w, w + NW, ... (or of four, a.block)
   f32x4 acc[G][XT], total[G][XT];
 #pragma unroll
   for (int g = 0; g < G; ++g)
@@ -711,6 +711,7 @@ __global__ __launch_bounds__(64 * kRowsWaves, 1) void gateup_rows_kernel(GemmArg
     n = mine == 0 ? 0 : 4 * mine - ((w + NW * (mine - 1) == nblocks - 1) ? 4 * nblocks - nchunks : 0);
   }
   if (n > 0) {
+    const int last = (ordered ? 4 : a.block) - 1;
     // past its last chunk a wave fetches that one again, so that every wait counts
     // the same number of younger transfers
 #pragma unroll
@@ -741,7 +742,7 @@ __global__ __launch_bounds__(64 * kRowsWaves, 1) void gateup_rows_kernel(GemmArg
           for (int g = 0; g < G; ++g)
             acc[g][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[g][j], fx[t][j], acc[g][t], 0, 0, 0);
       slot = slot + 1 == kSlots ? 0 : slot + 1;
-      if ((i & (ordered ? 3 : 7)) == (ordered ? 3 : 7) || i + 1 == n) end_block(w + NW * (i >> 2));
+      if ((i & last) == last || i + 1 == n) end_block(w + NW * (i >> 2));
     }
   }
   wait_vmcnt<0>();
@@ -965,9 +966,14 @@ GateupChoice gateup_choose(int32_t T, int32_t H, int32_t N2, bool act, bool alig
   // Other outputs, longer narrow ones among them, take the cheapest split: 2,056 x 4,096
   // x 512 takes 41.6 us unsplit, 24.0 us in three splits.
   const bool narrow = !act && N2 <= 2 * kBN && H % (4 * kBK) == 0 && H <= 8 * 4 * kBK;
+  // A choice of fewer splits than allowed makes no fp32 chain longer than the most
+  // splits would (`longest` stages): 256-row tiles, which keep one chain, take them all,
+  // and the others sum by blocks of four stages where eight would be longer.
+  const int longest = (H / kBK + max_splits - 1) / max_splits;
   Shape best;
   for (int bm : {256, 128, 64})
     for (int s = 1; s <= max_splits; ++s) {
+      if (bm == 256 && T >= 256 && s < max_splits) continue;
       if (narrow && ((s > 1 && s * 4 * kBK != H) || (bm == 256 && T >= 256))) continue;
       const Shape c = shape_cost(T, H, N2, grid_max, bm, s);
       if (c.items > INT32_MAX / 2) continue;
@@ -981,7 +987,7 @@ GateupChoice gateup_choose(int32_t T, int32_t H, int32_t N2, bool act, bool alig
   r.tail_m = best.tail_m;
   r.light = best.light;
   r.grid = int32_t(std::min<int64_t>(best.items, grid_max));
-  r.block = narrow ? 4 : 8;
+  r.block = narrow || longest < 8 ? 4 : 8;
   if (T > kRowsMaxT) return r;
   double cost = best.cost + kTilesBase;
   for (const RowsShape& v : kRowsShapes) {

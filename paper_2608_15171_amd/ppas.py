@@ -300,11 +300,12 @@ def gateup_proj(x, w, y, workspace=None, events: Events | None = None, stream=No
 def gateup_choice(n_tokens: int, hidden: int, n_out: int, activation: bool = False, aligned: bool = True,
                   workspace_bytes: int | None = None, num_cus: int = 0) -> dict:
     """The kernel a projection call takes (host only, for tests); workspace_bytes: None = as many as it can use."""
-    out = np.zeros(7, dtype=np.int32)
+    out = np.zeros(8, dtype=np.int32)
     nbytes = (1 << 62) if workspace_bytes is None else int(workspace_bytes)
     _check(_lib.ppas_gateup_choice(int(n_tokens), int(hidden), int(n_out), int(activation), int(aligned), nbytes,
                                    int(num_cus), _host_ptr(out)), "ppas_gateup_choice")
-    names = ("kernel", "rows", "main_tiles", "small_tiles", "weight_tiles", "weight_rows", "splits")
+    names = ("kernel", "rows", "main_tiles", "small_tiles", "weight_tiles", "weight_rows", "splits",
+             "block")
     c = dict(zip(names, out.tolist()))
     c["kernel"] = ("tiles", "rows", "general")[c["kernel"]]
     return c

@@ -384,6 +384,21 @@ def test_gateup_choice_query():
                     assert full["main_tiles"] * full["rows"] + 64 * (full["small_tiles"] - 1) < T
 
 
+@pytest.mark.parametrize("act,H,N", [(False, 11008, 2048), (False, 5504, 2048), (False, 2048, 2048), (False, 1024, 2048),
+                                     (False, 4096, 512), (True, 2048, 22016), (True, 3200, 6002), (True, 64, 150)])
+def test_fewer_splits_make_no_sum_longer(act, H, N):
+    """The most splits a call can take make its fp32 chains ceil(stages / splits) stages long, four
+    at least; a cheaper choice keeps to that, by sums of four or eight stages added to a total."""
+    stages = H // 64
+    for T in [*range(1, 520, 5), *range(520, 9000, 111)]:
+        most = max(1, ppas.gateup_workspace_bytes(T, H, N) // (4 * T * N))
+        c = ppas.gateup_choice(T, H, N, activation=act)
+        longest = -(-stages // most)
+        if c["kernel"] == "tiles" and c["rows"] == 256 and c["main_tiles"]:
+            assert -(-stages // c["splits"]) <= longest, (T, c, most)
+        assert c["block"] == 4 or c["block"] == 8 <= longest, (T, c, most)
+
+
 @pytest.mark.parametrize("num_cus", [256, 304, 64])
 def test_narrow_projections_split_into_whole_blocks(num_cus):
     """Up to 512 columns over a hidden size of one to eight 256-feature blocks: no split, or one
