@@ -871,13 +871,17 @@ struct Shape {
 };
 
 // Microseconds of one stage and, beside the stages, of one tile, by tile rows; of
-// the reducing launch, and of its partial sums' bytes; and the share by which a
-// full chip slows every stage. Fitted to 520 timed calls (64 to 8,200 tokens, the
-// decoder layer's four projections, every tile shape and split; 8 % rms), over
-// which the choice made with them is 0.8 % slower than the best one on average.
+// the reducing launch, for each split (its chain of loads), and of its partial sums'
+// bytes; and the share by which a full chip slows every stage. Fitted to 520 timed
+// calls (64 to 8,200 tokens, the decoder layer's four projections, every tile shape
+// and split; 8 % rms), over which the choice made with them is 0.8 % slower than the
+// best one on average. kWeightBytes, the rate that the weights come in no faster than,
+// and kReduceSplit (more rows hide the chain) belong to the fit at rows_cost.
 constexpr double kStage256 = 0.92, kStage128 = 0.66, kStage64 = 0.53;
 constexpr double kTile256 = 5.3, kTile128 = 1.4, kTile64 = 0.4;
-constexpr double kReduce = 4.25, kPartBytes = 5.5e6, kLoaded = 0.186;
+constexpr double kReduce = 4.25, kReduceSplit = 0.12, kPartBytes = 5.5e6, kLoaded = 0.186, kWeightBytes = 9.45e6;
+
+constexpr int kRowsMaxT = 256;   // the few-row kernel measured up to here; from about 64 rows the tiles win on wide outputs
 
 Shape shape_cost(int32_t T, int32_t H, int32_t N2, int grid_max, int bm, int splits) {
   Shape s;
@@ -899,8 +903,9 @@ Shape shape_cost(int32_t T, int32_t H, int32_t N2, int grid_max, int bm, int spl
   const int64_t extra = (ns - in_light + grid - 1) / grid;
   const double t_light = double(nf / grid) * cf + double((in_light + light - 1) / light + extra) * cs;
   const double t_heavy = rem ? double(nf / grid + 1) * cf + double(extra) * cs : 0;
-  s.cost = std::max(t_light, t_heavy) * (1 + kLoaded * std::min(1.0, double(s.items) / grid_max));
-  if (splits > 1) s.cost += kReduce + 2.0 * splits * double(T) * N2 * 4 / kPartBytes;
+  s.cost = std::max(std::max(t_light, t_heavy) * (1 + kLoaded * std::min(1.0, double(s.items) / grid_max)),
+                    2.0 * N2 * H / kWeightBytes);
+  if (splits > 1) s.cost += kReduce + (T <= kRowsMaxT ? kReduceSplit * splits : 0) + 2.0 * splits * double(T) * N2 * 4 / kPartBytes;
   return s;
 }
 
@@ -912,14 +917,20 @@ struct RowsShape {
 };
 constexpr RowsShape kRowsShapes[] = {{1, 8, false, true}, {1, 16, false, true}, {2, 8, true, false},
                                      {2, 16, true, true}, {4, 16, true, true},  {6, 16, true, true}};
-constexpr int kRowsMaxT = 256;   // measured up to here; from about 64 rows the tiles win on wide outputs
 
-// Microseconds: the weights stream at 5.8 TB/s over the chip or 110 GB/s into one
-// compute unit, X (from L2) at 114 GB/s, one after the other; the rest is the
-// launch and the workgroup's fill and final sums. Fitted with kTilesBase, the
-// launches of a call of the tile kernels, to 460 timed calls (1 to 256 tokens, ten
-// projections; 13 % rms), over which the choice is 0.7 % slower than the best.
-constexpr double kTilesBase = 7.5;
+// Microseconds: the weights stream at 8 TB/s over the chip or 56 GB/s into one compute
+// unit, X (from L2) at 99 GB/s, one after the other; every round of resident workgroups
+// takes 2.8 us to fill; the rest is the launch and the final sums. Where variants come
+// out alike, more workgroups of fewer weight-row tiles have more loads in flight: 8,192
+// x 8,192 with one token 30.0 us in one tile against 32.9 in two. Fitted with
+// kTilesBase, the launches of a call of the tile kernels, to 14,500 timed calls (60
+// projections, 1 to 1,000 tokens, every variant, the weights from memory: none is read
+// again before 640 MB of others; 15 % rms, the tiles 14 %). The choice is then 1.5 %
+// slower than the best on average. Constants fitted to weights that a repeated call
+// finds in the 256 MB cache made it 3.6 %, and some calls slower than one tile kernel
+// for all sizes had been: 11,008 x 512 with 48 tokens 24.2 us where that one takes 22.3
+// (now 18.9), 16,384 x 8,192 with 16 tokens 82.4 against 73.8 (now 65.2).
+constexpr double kTilesBase = 4.64;
 double rows_cost(int32_t T, int32_t H, int32_t N2, int cus, const RowsShape& v) {
   const int xt = rows_tokens(T) / 16;
   const double cols = double((int64_t(N2) + v.g * v.wr - 1) / (v.g * v.wr));
@@ -929,8 +940,10 @@ double rows_cost(int32_t T, int32_t H, int32_t N2, int cus, const RowsShape& v) 
   const int per_cu = std::max(1, kSmem / std::max(ring, 4 * v.g * xt * 1024));
   const double wgs = cols * mt, room = double(cus) * per_cu;
   const double rounds = wgs > room ? std::ceil(wgs / room) * per_cu : std::max(1.0, wgs / cus);
-  const double w = 2.0 * v.g * v.wr * H, x = 2.0 * std::min(T, 16 * xt) * H;
-  return 2.4 + std::max(rounds * w / 1.1e5, mt * 2.0 * N2 * H / 5.8e6) + rounds * x / 1.14e5 + 0.11 * v.g * xt;
+  const double w = 2.0 * v.g * v.wr * H, x = 2.0 * T / mt * H;
+  const double cost = 2.9 + std::max(rounds * w / 5.57e4, mt * 2.0 * N2 * H / 8.0e6) + rounds * x / 9.93e4 +
+                      0.02 * v.g * xt + 2.84 * std::ceil(wgs / room);
+  return cost * (1 + 0.01 * (v.g - 1));
 }
 
 }  // namespace

@@ -384,6 +384,20 @@ def test_gateup_choice_query():
                     assert full["main_tiles"] * full["rows"] + 64 * (full["small_tiles"] - 1) < T
 
 
+@pytest.mark.parametrize("T,H,N,kernel,most_splits", [
+    # us cold, the choice of constants fitted to cached weights against the one that stands
+    (48, 11008, 512, "tiles", 32),      # few rows 24.2, 24 splits 18.9
+    (48, 11008, 256, "tiles", 32),      # few rows 24.0, 26 splits 18.4
+    (48, 11008, 2048, "tiles", 24),     # few rows 27.0, 19 splits 21.6
+    (16, 16384, 8192, "tiles", 6),      # 8 splits 82.4, 6 splits 65.2
+    (28, 8192, 8192, "tiles", 6),       # 8 splits 35.5, 6 splits 32.2
+    (1, 18944, 3584, "rows", 1)])       # tiles 32.0, few rows 25.1
+def test_gateup_choice_is_for_weights_from_memory(T, H, N, kernel, most_splits):
+    """A model's weights come from memory, not from the cache that a repeated call finds them in."""
+    c = ppas.gateup_choice(T, H, N)
+    assert c["kernel"] == kernel and c["splits"] <= most_splits, c
+
+
 @pytest.mark.parametrize("act,H,N", [(False, 11008, 2048), (False, 5504, 2048), (False, 2048, 2048), (False, 1024, 2048),
                                      (False, 4096, 512), (True, 2048, 22016), (True, 3200, 6002), (True, 64, 150)])
 def test_fewer_splits_make_no_sum_longer(act, H, N):
