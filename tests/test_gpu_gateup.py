@@ -122,14 +122,14 @@ def test_zero_tokens_is_a_no_op_and_bad_sizes_are_refused(lib):
 
 
 @pytest.mark.parametrize("T,H,N", [
-    # 64-row tiles only: one row over a tile; single-stage tiles, several per workgroup
+    # one row over a tile; single-stage tiles, several per workgroup
     (65, 64, 300), (449, 64, 22016), (1790, 64, 9000),
-    # 128-row tiles, then 64-row tiles of the last rows; three stages; splits
+    # a few rows after whole tiles; three stages; splits
     (130, 2048, 22010), (513, 192, 22000), (700, 11008, 2048),
-    # 256-row tiles, then 64-row tiles dealt to the workgroups with fewer of them
+    # 64-row tiles dealt to the workgroups with fewer large ones; a narrow output
     (321, 2048, 22016), (577, 1024, 16000), (2048, 11008, 300)])
 def test_tile_shapes_every_element(lib, T, H, N):
-    """Sizes at which each tile shape is chosen, with ragged rows, columns and stage counts."""
+    """Ragged rows, columns and stage counts of the tile kernels."""
     print(f"gate-up tiles T={T} H={H} N={N}", flush=True)
     xb = I.gateup_tokens(6, T, 0, hidden=H)
     wb = I.gateup_weight(6, hidden=H, inter=(N + 1) // 2)[:N]
@@ -158,8 +158,8 @@ def test_operands_off_the_16_byte_grid(lib, which):
 
 
 @pytest.mark.parametrize("T,H,N", [
-    # few rows: 16-, 32- and 64-row tiles and their edges, several of them; one to six weight-row tiles per
-    # workgroup; a last block of one chunk; fewer chunks than waves; more blocks than are kept in order
+    # few rows: 16-, 32- and 64-row tiles and their edges, several of them; a last block of one chunk; fewer
+    # chunks than waves; more blocks than are kept in order
     (1, 2048, 22016), (16, 2048, 2050), (17, 64, 300), (24, 11008, 2048), (33, 576, 256), (48, 2048, 11010),
     (64, 128, 40), (65, 2048, 2048), (100, 2112, 130), (256, 2048, 250), (20, 192, 9001)])
 def test_few_rows_every_element(lib, T, H, N):
@@ -167,6 +167,67 @@ def test_few_rows_every_element(lib, T, H, N):
     xb = I.gateup_tokens(9, T, 0, hidden=H)
     wb = I.gateup_weight(9, hidden=H, inter=(N + 1) // 2)[:N]
     check(f64(lib, run(lib, xb, wb)), xb, wb, label=f"T{T} H{H} N{N}")
+
+
+# Every kernel variant, with the choice that names it: few rows by token rows per workgroup, weight-row tiles and
+# their rows; tiles by the rows of a main tile (64: small tiles only), whether the reduction is split and whether
+# small tiles follow. Columns, rows and stages are ragged where the variant allows it.
+VARIANTS = [
+    ("rows", 16, 1, 8, 16, 11008, 1697), ("rows", 16, 1, 16, 10, 11008, 2730), ("rows", 16, 2, 16, 10, 5504, 5445),
+    ("rows", 16, 4, 16, 14, 2048, 10463), ("rows", 16, 6, 16, 16, 2048, 22016), ("rows", 32, 1, 8, 18, 11008, 1516),
+    ("rows", 32, 1, 16, 30, 3584, 2790), ("rows", 32, 2, 16, 18, 3008, 5541), ("rows", 32, 4, 16, 29, 1024, 10102),
+    ("rows", 32, 6, 16, 24, 2048, 22016), ("rows", 64, 1, 8, 250, 3008, 399), ("rows", 64, 1, 16, 168, 1600, 1116),
+    ("rows", 64, 2, 16, 172, 1024, 1703), ("rows", 64, 4, 16, 187, 576, 2784), ("rows", 64, 6, 16, 67, 576, 8270),
+    ("rows", 64, 6, 16, 48, 2048, 22016),
+    ("tiles", 64, False, True, 193, 192, 8096), ("tiles", 64, True, True, 545, 3008, 183),
+    ("tiles", 128, False, False, 256, 128, 16872), ("tiles", 128, False, True, 131, 128, 21995),
+    ("tiles", 128, True, False, 1408, 2048, 360), ("tiles", 128, True, True, 1190, 11008, 23),
+    ("tiles", 256, False, False, 768, 320, 10756), ("tiles", 256, False, True, 583, 320, 21776),
+    ("tiles", 256, True, False, 1792, 11008, 1064), ("tiles", 256, True, True, 513, 11008, 3102)]
+
+
+def variant_of(c):
+    if c["kernel"] == "rows":
+        return "rows", c["rows"], c["weight_tiles"], c["weight_rows"]
+    return c["kernel"], c["rows"] if c["main_tiles"] else 64, c["splits"] > 1, c["small_tiles"] > 0
+
+
+@pytest.mark.parametrize("kind,rows,p,q,T,H,N", VARIANTS)
+def test_every_variant_every_element(lib, kind, rows, p, q, T, H, N):
+    ppas = lib[0]
+    assert variant_of(ppas.gateup_choice(T, H, N, num_cus=256)) == (kind, rows, p, q)
+    print(f"gate-up {kind} {rows} {p} {q} T={T} H={H} N={N}", flush=True)
+    xb = I.gateup_tokens(12, T, 0, hidden=H)
+    wb = I.gateup_weight(12, hidden=H, inter=(N + 1) // 2)[:N]
+    check(f64(lib, run(lib, xb, wb)), xb, wb, label=f"{kind} {rows} {p} {q}")
+
+
+@pytest.mark.parametrize("T,H,N,split", [(1, 64, 1, False), (257, 128, 513, True), (40, 2048, 520, True),
+                                         (40, 2048, 520, False), (300, 11008, 1030, True), (700, 640, 1031, True)])
+@pytest.mark.parametrize("which", ["x", "w", "xw"])
+def test_general_kernel_every_element(lib, which, T, H, N, split):
+    """Operands off the 16-byte grid, with and without the workspace: one chain per split."""
+    ppas, step, torch = lib
+    nbytes = ppas.gateup_workspace_bytes(T, H, N) if split else 0
+    c = ppas.gateup_choice(T, H, N, aligned=False, workspace_bytes=nbytes)
+    assert c["kernel"] == "general" and (c["splits"] > 1) == (split and H > 256 and T * N > 1), c
+    print(f"gate-up general {which} T={T} H={H} N={N} splits={c['splits']}", flush=True)
+    xb = I.gateup_tokens(13, T, 0, hidden=H)
+    wb = I.gateup_weight(13, hidden=H, inter=(N + 1) // 2)[:N]
+
+    def put(bits, off):
+        flat = torch.zeros(bits.size + 4, dtype=torch.bfloat16, device="cuda")
+        v = flat[4:] if off else flat[:-4]
+        v.copy_(step.to_device_bf16(bits).flatten())
+        return v.view(*bits.shape)
+
+    x, w = put(xb, "x" in which), put(wb, "w" in which)
+    assert (x.data_ptr() | w.data_ptr()) % 16 == 8
+    y = torch.full((T, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = torch.full((nbytes // 4,), float("nan"), dtype=torch.float32, device="cuda") if nbytes else None
+    ppas.gateup_proj(x, w, y, ws)
+    torch.cuda.synchronize()
+    check(f64(lib, y), xb, wb, label=f"general {which} T{T} H{H} N{N} split={split}")
 
 
 @pytest.mark.parametrize("H,N", [(2048, 256), (2048, 512), (1024, 500), (256, 128)])

@@ -130,7 +130,7 @@ def test_shapes_and_sizes_are_refused(lib):
 @pytest.mark.parametrize("T,H,NI", [(65, 64, 150), (130, 2048, 11005), (513, 192, 11000), (321, 2048, 11008),
                                     (577, 1024, 8000), (700, 2048, 1030)])
 def test_tile_shapes_every_element(lib, T, H, NI):
-    """Sizes at which each tile shape is chosen, with ragged rows, features and stage counts."""
+    """Ragged rows, features and stage counts of the tile kernels."""
     print(f"gate-up-act tiles T={T} H={H} I={NI}", flush=True)
     xb = I.gateup_tokens(8, T, 0, hidden=H)
     wb = I.gateup_weight(8, hidden=H, inter=NI)
@@ -140,8 +140,64 @@ def test_tile_shapes_every_element(lib, T, H, NI):
 @pytest.mark.parametrize("T,H,NI", [(1, 2048, 11008), (16, 64, 500), (17, 1024, 3001), (24, 2048, 5504),
                                     (64, 576, 1500), (65, 128, 700), (200, 2048, 640)])
 def test_few_rows_every_element(lib, T, H, NI):
-    """Few rows: tiles of 16, 32 and 64 rows and two to six weight-row tiles per workgroup."""
+    """Few rows: tiles of 16, 32 and 64 rows and their edges."""
     print(f"gate-up-act rows T={T} H={H} I={NI}", flush=True)
     xb = I.gateup_tokens(11, T, 0, hidden=H)
     wb = I.gateup_weight(11, hidden=H, inter=NI)
     check(f64(run(lib, xb, wb)), xb, wb, label=f"act T{T} H{H} I{NI}")
+
+
+# Every kernel variant, with the choice that names it: few rows by token rows per workgroup, weight-row tiles and
+# their rows; tiles by the rows of a main tile (64: small tiles only), whether the reduction is split and whether
+# small tiles follow.
+VARIANTS = [
+    ("rows", 16, 2, 8, 9, 11008, 1514), ("rows", 16, 2, 16, 13, 3008, 3836), ("rows", 16, 4, 16, 8, 3008, 6233),
+    ("rows", 16, 6, 16, 8, 2112, 8874), ("rows", 32, 2, 8, 30, 3584, 1395), ("rows", 32, 2, 16, 21, 3008, 2375),
+    ("rows", 32, 4, 16, 25, 1024, 5864), ("rows", 32, 6, 16, 24, 2048, 11008), ("rows", 64, 2, 8, 208, 5504, 131),
+    ("rows", 64, 2, 16, 88, 1024, 1665), ("rows", 64, 4, 16, 139, 576, 1873), ("rows", 64, 6, 16, 70, 576, 4183),
+    ("rows", 64, 6, 16, 48, 2048, 11008),
+    ("tiles", 64, False, True, 228, 320, 2056), ("tiles", 64, True, True, 775, 3584, 54),
+    ("tiles", 128, False, False, 256, 128, 8197), ("tiles", 128, False, True, 129, 128, 10982),
+    ("tiles", 128, True, False, 1024, 11008, 133), ("tiles", 128, True, True, 1136, 11008, 12),
+    ("tiles", 256, False, False, 768, 320, 5600), ("tiles", 256, False, True, 611, 320, 10889),
+    ("tiles", 256, True, False, 1280, 5504, 1549), ("tiles", 256, True, True, 2076, 11008, 387)]
+
+
+@pytest.mark.parametrize("kind,rows,p,q,T,H,NI", VARIANTS)
+def test_every_variant_every_element(lib, kind, rows, p, q, T, H, NI):
+    c = lib[0].gateup_choice(T, H, 2 * NI, activation=True, num_cus=256)
+    got = (c["rows"], c["weight_tiles"], c["weight_rows"]) if c["kernel"] == "rows" else \
+        (c["rows"] if c["main_tiles"] else 64, c["splits"] > 1, c["small_tiles"] > 0)
+    assert (c["kernel"], *got) == (kind, rows, p, q)
+    print(f"gate-up-act {kind} {rows} {p} {q} T={T} H={H} I={NI}", flush=True)
+    xb = I.gateup_tokens(14, T, 0, hidden=H)
+    wb = I.gateup_weight(14, hidden=H, inter=NI)
+    check(f64(run(lib, xb, wb)), xb, wb, label=f"act {kind} {rows} {p} {q}")
+
+
+@pytest.mark.parametrize("T,H,NI,split", [(1, 64, 1, False), (257, 128, 257, True), (40, 2048, 260, True),
+                                          (40, 2048, 260, False), (300, 11008, 515, True), (700, 640, 513, True)])
+@pytest.mark.parametrize("which", ["x", "w", "xw"])
+def test_general_kernel_every_element(lib, which, T, H, NI, split):
+    """Operands off the 16-byte grid, with and without the workspace: one chain per split."""
+    ppas, step, torch = lib
+    nbytes = ppas.gateup_act_workspace_bytes(T, H, NI) if split else 0
+    c = ppas.gateup_choice(T, H, 2 * NI, activation=True, aligned=False, workspace_bytes=nbytes)
+    assert c["kernel"] == "general" and (c["splits"] > 1) == (split and H > 256), c
+    print(f"gate-up-act general {which} T={T} H={H} I={NI} splits={c['splits']}", flush=True)
+    xb = I.gateup_tokens(15, T, 0, hidden=H)
+    wb = I.gateup_weight(15, hidden=H, inter=NI)
+
+    def put(bits, off):
+        flat = torch.zeros(bits.size + 4, dtype=torch.bfloat16, device="cuda")
+        v = flat[4:] if off else flat[:-4]
+        v.copy_(step.to_device_bf16(bits).flatten())
+        return v.view(*bits.shape)
+
+    x, w = put(xb, "x" in which), put(wb, "w" in which)
+    assert (x.data_ptr() | w.data_ptr()) % 16 == 8
+    y = torch.full((T, NI), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = torch.full((nbytes // 4,), float("nan"), dtype=torch.float32, device="cuda") if nbytes else None
+    ppas.gateup_act(x, w, y, ws)
+    torch.cuda.synchronize()
+    check(f64(y), xb, wb, label=f"act general {which} T{T} H{H} I{NI} split={split}")
