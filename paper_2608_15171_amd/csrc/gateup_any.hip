@@ -46,58 +46,34 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "device.h"
+#include "gateup_device.h"
+
 namespace ppas {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void global_cvoid;
 
-#ifndef PPAS_GATEUP_BK
-#define PPAS_GATEUP_BK 64
-#endif
-#ifndef PPAS_GATEUP_RING
-#define PPAS_GATEUP_RING 2
-#endif
-#ifndef PPAS_GATEUP_SPREAD
-#define PPAS_GATEUP_SPREAD 2
-#endif
-#ifndef PPAS_GATEUP_WAVES
-#define PPAS_GATEUP_WAVES 8
-#endif
-constexpr int kWaves = PPAS_GATEUP_WAVES;  // waves per workgroup: one or two per SIMD
-static_assert(kWaves == 4 || kWaves == 8, "four or eight waves");
+constexpr int kWaves = 8;                // two per SIMD
 constexpr int kThreads = 64 * kWaves;
 constexpr int kBM = 256;                 // token rows per tile
 constexpr int kBMTail = 64;              // token rows per tile of the last T % 256 rows
 constexpr int kBN = 256;                 // output columns per tile
-constexpr int kBK = PPAS_GATEUP_BK;     // features per stage
+constexpr int kBK = 64;                  // features per stage
 constexpr int kKSteps = kBK / 16;        // MFMA k-steps per stage
-constexpr int kRing = PPAS_GATEUP_RING;  // stages in the LDS ring; transfers run kRing - 1 stages ahead
+constexpr int kRing = 2;                 // stages in LDS; transfers run one stage ahead
 constexpr int kCPR = kBK / 8;            // 16-byte chunks of a row per stage
 constexpr int kRowBytes = 16 * kCPR;
 constexpr int kRowsPerDma = 64 / kCPR;   // whole rows covered by one 64-lane 16-byte transfer
 constexpr int kPart = 256 * kRowBytes;   // the 256 W (or X) rows of one stage
 constexpr int kStage = 2 * kPart;
-static_assert(kBK == 32 || kBK == 64, "stages of 32 or 64 features");
-static_assert(kRing >= 2 && kRing <= 5, "a ring of two to five stages");
-constexpr int kSpread = PPAS_GATEUP_SPREAD < kKSteps ? PPAS_GATEUP_SPREAD : kKSteps;   // k-steps that issue the next stage
+constexpr int kSpread = 2;               // k-steps that issue the next stage
 constexpr int kPitch = 128 * 2 + 16;     // epilogue LDS row pitch in bytes (16-byte aligned, padded)
 constexpr int kEpiWave = (kBM * 2 / kWaves) * kPitch;   // one wave's output block of a full tile (<= 128 columns)
 constexpr int kSmem = (kRing * kStage > kWaves * kEpiWave) ? kRing * kStage : kWaves * kEpiWave;
 static_assert(kSmem <= 160 * 1024, "the LDS of one compute unit");
 constexpr int kGroupM = 8;               // token-row tiles per tile-order group
-#ifndef PPAS_GATEUP_PERSIST
-#define PPAS_GATEUP_PERSIST 1
-#endif
-constexpr bool kPersist = PPAS_GATEUP_PERSIST;   // a workgroup per compute unit, looping over tiles
-
 
 struct GemmArgs {
   const uint16_t* x;
@@ -111,79 +87,28 @@ struct GemmArgs {
   int32_t I;                  // with the gated activation: N2 / 2 intermediate features
 };
 
-__device__ __forceinline__ u32x4 lds16(const char* p) { return *reinterpret_cast<const u32x4*>(p); }
-
 // LDS row layout of a stage: row R's 16-byte chunk c sits at position
 // c ^ swizzle(R). Sixteen consecutive rows span 256 bytes' worth of banks in
 // kRowBytes-sized rows, and the swizzle gives each of them a different position
 // for the same chunk, so the 16 lanes an operand read serves per cycle hit 16
 // different 16-byte bank groups.
 __device__ __forceinline__ int swizzle(int R) { return (R / (16 / kCPR)) % kCPR; }
-__device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
-
-__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
-  const f32x2 v = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
-// silu(g) = g / (1 + e^-g) in fp32 (e^-g through the hardware base-2 exponential;
-// +inf for large negative g, which gives -0).
-__device__ __forceinline__ float silu_f32(float g) {
-  return g / (1.f + __builtin_amdgcn_exp2f(-g * 1.4426950408889634f));
-}
 
 // 16 bytes from global memory into LDS: lane L of the wave lands at lds + 16 L.
 __device__ __forceinline__ void dma16(const uint16_t* g, char* lds) {
   __builtin_amdgcn_global_load_lds((global_cvoid*)g, (lds_void*)lds, 16, 0, 0);
 }
 
-__device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }
-
-// Wait until at most `later` stages of PER transfers each are still in flight
-// (vmcnt: bits 3:0 and 15:14 of the s_waitcnt immediate).
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
-template <int PER>
-__device__ __forceinline__ void wait_stages(int later) {
-  static_assert((kRing - 2) * PER < 64, "the transfers in flight fit the vmcnt counter");
-  if (later >= 3)
-    wait_vmcnt<(kRing >= 5 ? 3 * PER : 0)>();
-  else if (later == 2)
-    wait_vmcnt<2 * PER>();
-  else if (later == 1)
-    wait_vmcnt<PER>();
-  else
-    wait_vmcnt<0>();
-}
-
-// Workgroup barrier without a memory fence (the fence of __syncthreads would also
-// wait for the transfers still in flight for later stages). The LDS data it
-// guards is written only by the transfers, whose completion each wave waits for
-// explicitly; the empty asm keeps the compiler from moving memory accesses
-// across it.
-__device__ __forceinline__ void bare_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("" ::: "memory");
-}
-
 // One output tile of BM token rows x 256 columns over stages k_lo .. k_hi - 1.
 // BM = 256 (full tiles) or 64 (the ragged last rows of the tokens, and calls of
 // fewer than 256 tokens). Wave (wn, wm) owns a WN x WM block of it (columns x
-// token rows) as kNT x kMT MFMA tiles of 32 x 32:
-//   four waves:  128 x 128 (full), 128 x 32 (tail)
-//   eight waves: 128 x 64 (full),   64 x 32 (tail)
+// token rows) as kNT x kMT MFMA tiles of 32 x 32: 128 x 64 (full) or 64 x 32 (tail).
 // The W part of a stage is always 256 rows, the X part BM rows; the first half
 // of the waves copy the W part, the second half the X part, in equal shares.
 template <int BM, bool kAct>
 __device__ __forceinline__ void tile_body(const GemmArgs& a, char* smem, int m0, int n0, int split, int k_lo,
                                           int k_hi) {
-  constexpr int WN = (BM == kBM || kWaves == 4) ? 128 : 64;   // columns per wave
+  constexpr int WN = BM == kBM ? 128 : 64;   // columns per wave
   constexpr int NG = kBN / WN;                                // column groups
   constexpr int WM = BM / (kWaves / NG);                      // token rows per wave
   constexpr int kNT = WN / 32, kMT = WM / 32;                 // MFMA tiles per wave
@@ -268,16 +193,11 @@ __device__ __forceinline__ void tile_body(const GemmArgs& a, char* smem, int m0,
   for (int s = 0; s < kRing - 1; ++s)
     if (k_lo + s < k_hi) issue_all(k_lo + s);
 
-  // Entering stage s: this wave's transfers of stage s are done once at most
-  // those of the stages after it are still in flight; the barrier then makes
-  // every wave's part visible and tells that stage s - 1, whose ring slot the
+  // Entering stage s: this wave's transfers of the stage are done; the barrier then
+  // makes every wave's part visible and tells that stage s - 1, whose ring slot the
   // next transfers overwrite, has been read by all waves.
-  auto enter = [&](int s) {
-    const int later = min(k_hi - 1 - s, kRing - 2);
-    if (is_x)
-      wait_stages<kDmaX>(later);
-    else
-      wait_stages<kDmaMax>(later);
+  auto enter = [] {
+    wait_vmcnt<0>();
     bare_barrier();
   };
   // Operand fragments, double-buffered over k-steps. A k-step's eight reads go
@@ -309,7 +229,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& a, char* smem, int m0,
   static_assert(kKSteps % 2 == 0, "k-steps alternate the two fragment buffers");
 
   if (k_lo < k_hi) {
-    enter(k_lo);
+    enter();
     read_a(k_lo, 0, 0);
     read_b(k_lo, 0, 0);
   }
@@ -317,7 +237,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& a, char* smem, int m0,
     // The transfers of stage s + kRing - 1 go into the slot of stage s - 1, which
     // every wave has finished reading (the barrier of entering s). Past the last
     // stage they repeat stage k_hi - 1 into that free slot, which keeps the loop
-    // free of branches around them; the waits count them as stages in flight.
+    // free of branches around them.
     const int sd = min(s + kRing - 1, k_hi - 1);
     const int slot = (s + kRing - 1) % kRing;
 #pragma unroll
@@ -346,7 +266,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& a, char* smem, int m0,
       __builtin_amdgcn_sched_barrier(0);
       if (last) {
         if (s + 1 < k_hi) {
-          enter(s + 1);
+          enter();
           read_a(s + 1, 0, 0);
           read_b(s + 1, 0, 0);
         }
@@ -356,7 +276,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& a, char* smem, int m0,
       }
     }
   }
-  wait_vmem();   // the repeated transfers of the last stages have landed
+  wait_vmcnt<0>();   // the repeated transfers of the last stages have landed
   __syncthreads();   // every wave is done with the ring before it holds the output
 
   // Result register r of MFMA tile (ti, tj): token row 32 tj + L % 32 of the
@@ -387,15 +307,8 @@ __device__ __forceinline__ void tile_body(const GemmArgs& a, char* smem, int m0,
             lim = ti < kNT / 2 ? a.I : a.N2;
             vec = (a.I & 3) == 0;
           }
-          float* dst = pb + size_t(m) * a.N2 + n;
-          if (n + 4 <= lim && vec) {
-            *reinterpret_cast<f32x4*>(dst) =
-                f32x4{acc[ti][tj][4 * g], acc[ti][tj][4 * g + 1], acc[ti][tj][4 * g + 2], acc[ti][tj][4 * g + 3]};
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (n + e < lim) dst[e] = acc[ti][tj][4 * g + e];
-          }
+          store_part(pb + size_t(m) * a.N2, n, lim, vec,
+                     f32x4{acc[ti][tj][4 * g], acc[ti][tj][4 * g + 1], acc[ti][tj][4 * g + 2], acc[ti][tj][4 * g + 3]});
         }
       }
     return;
@@ -573,8 +486,7 @@ hipError_t launch_gateup_any(const uint16_t* x, const uint16_t* w, uint16_t* y, 
   if (n <= 0 || n > INT32_MAX) return hipErrorInvalidValue;
   // one workgroup per compute unit, each looping over its items (a multiple of 8
   // workgroups, so that every workgroup stays on one XCD's share of the items)
-  const int64_t slots = kPersist ? std::max(8, cus / 8 * 8) : n;
-  const int64_t grid = std::min<int64_t>(n, slots);
+  const int64_t grid = std::min<int64_t>(n, std::max(8, cus / 8 * 8));
   if (act)
     hipExtLaunchKernelGGL(gateup_any_kernel<true>, dim3(unsigned(grid)), dim3(kThreads), 0, stream, ev_start, ev_stop,
                           0, a);
