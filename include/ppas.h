@@ -325,9 +325,11 @@ int32_t ppas_plan_items(const ppas_shape* shape, const ppas_seq* seqs, int32_t n
  * the caller's workspace (ppas_gateup_workspace_bytes, device memory, not read
  * before written, not shared with a call still in flight) and a second launch
  * adds them in a fixed order. A workspace smaller than that (NULL with 0 bytes
- * included) gives fewer splits, down to none: results are deterministic for a
- * given shape and workspace size, and every split count stays within the same
- * rounding bound. The kernels run on hip_stream (events: start on the first
+ * included) gives fewer splits, down to none. The kernel, and with it the order of
+ * the sums, is chosen by the shape, the workspace size, the device's compute units
+ * and whether x and w both start on a 16-byte boundary: results are deterministic
+ * where these are the same, and every choice stays within the same rounding bound.
+ * The kernels run on hip_stream (events: start on the first
  * launch, stop on the last, as for the other calls; may be NULL); no host sync.
  * hidden must be a positive multiple of 64 (PPAS_EUNSUPPORTED otherwise);
  * n_tokens == 0 is a no-op; NULL pointers (a NULL workspace with a non-zero
@@ -338,9 +340,11 @@ ppas_status ppas_gateup_proj(const void* x, const void* w, void* y, int32_t n_to
                              int32_t n_out, void* workspace, size_t workspace_bytes,
                              const ppas_events* events, void* hip_stream);
 
-/* Workspace ppas_gateup_proj uses for this shape on the current device (0 when
- * it does not split the reduction, or for an invalid shape). The library's own
- * sizing call: the paper describes no workspace. */
+/* The most workspace ppas_gateup_proj can use for this shape on the current device
+ * (0 when it does not split the reduction, or for an invalid shape): that of about
+ * one workgroup per compute unit. Aligned operands often take fewer splits and
+ * touch less of it. The library's own sizing call: the paper describes no
+ * workspace. */
 size_t ppas_gateup_workspace_bytes(int32_t n_tokens, int32_t hidden, int32_t n_out);
 
 /*
@@ -363,9 +367,9 @@ ppas_status ppas_gateup_act(const void* x, const void* w, void* y, int32_t n_tok
                             int32_t n_inter, void* workspace, size_t workspace_bytes,
                             const ppas_events* events, void* hip_stream);
 
-/* Workspace ppas_gateup_act uses for this shape on the current device (0 when it
- * does not split the reduction, or for an invalid shape). The library's own
- * sizing call. */
+/* The most workspace ppas_gateup_act can use for this shape on the current device
+ * (0 when it does not split the reduction, or for an invalid shape). The library's
+ * own sizing call. */
 size_t ppas_gateup_act_workspace_bytes(int32_t n_tokens, int32_t hidden, int32_t n_inter);
 
 /*
