@@ -34,7 +34,7 @@ SOURCES = {
     "attn_step_kernel": ["paper_2608_15171_amd/csrc/attn_step.hip", "paper_2608_15171_amd/csrc/plan.cpp",
                          "paper_2608_15171_amd/csrc/plan.h"],
     "rope_append_kernel": ["paper_2608_15171_amd/csrc/rope_append.hip"],
-    "gateup_kernel": ["paper_2608_15171_amd/csrc/gateup.hip"],
+    "gateup_kernel": ["paper_2608_15171_amd/csrc/gateup.hip", "paper_2608_15171_amd/csrc/gateup_device.h"],
 }
 DESCRIPTION = {
     "attn_step_kernel": "One packed attention launch of the mixed step on one MI355X (gfx950); bf16 inputs, fp32 "
@@ -145,8 +145,9 @@ def main(workload: str, d: str, calib: str, kernel: str = "attn_step_kernel"):
     print(out + ".md")
 
 
-MFMA_COUNTERS = ["GRBM_GUI_ACTIVE", "SQ_WAVE_CYCLES", "SQ_BUSY_CYCLES", "SQ_VALU_MFMA_BUSY_CYCLES", "SQ_INSTS_MFMA",
-                 "SQ_INSTS_VALU", "SQ_INSTS_LDS", "SQ_LDS_IDX_ACTIVE", "SQ_LDS_BANK_CONFLICT"]
+MFMA_COUNTERS = ["GRBM_GUI_ACTIVE", "SQ_WAVE_CYCLES", "SQ_INSTS_VALU_MFMA_MOPS_BF16", "SQ_VALU_MFMA_BUSY_CYCLES",
+                 "SQ_INSTS_MFMA", "SQ_INSTS_VALU", "SQ_INSTS_LDS", "SQ_LDS_IDX_ACTIVE", "SQ_LDS_BANK_CONFLICT"]
+MOP_FLOP = 512      # of one count of SQ_INSTS_VALU_MFMA_MOPS_BF16, whatever the instruction's shape
 
 
 def mfma_summary(workload: str, d: str, kernel: str = "", simds: int = 1024, xcds: int = 8):
@@ -170,11 +171,7 @@ def mfma_summary(workload: str, d: str, kernel: str = "", simds: int = 1024, xcd
     cycles = m["GRBM_GUI_ACTIVE"] / xcds
     clock = cycles / us / 1e3
     busy = m["SQ_VALU_MFMA_BUSY_CYCLES"] / (simds * cycles)
-    # the projection and the eight-wave attention kernel run 16x16x32 MFMAs only, the four-wave one 32x32x16 ones
-    # (its decode items' 16x16x32 MFMAs then count double)
-    small = kernel == "gateup_kernel" or any("<8>" in r["Kernel_Name"] for r in rows if kernel in r["Kernel_Name"])
-    per_mfma = 16384 if small else 32768
-    mfma_flop = m["SQ_INSTS_MFMA"] * per_mfma
+    mfma_flop = m["SQ_INSTS_VALU_MFMA_MOPS_BF16"] * MOP_FLOP
     cmd = (f"cd /tmp && TMPDIR=/tmp rocprofv3 --pmc {' '.join(MFMA_COUNTERS)} --output-format csv -d <out> -o run "
            f"-- python3 <repo>/bench.py --workload {workload}{_sec(kernel)} --no-cpu-baseline --no-attainable --steps 3 --warmup-seconds 0.5")
     lines = [f"# {kernel} -- matrix-core utilisation, workload {bench['config']['workload']} ({workload})", "",
@@ -183,7 +180,7 @@ def mfma_summary(workload: str, d: str, kernel: str = "", simds: int = 1024, xcd
              f"| kernel time under the profiler | {us:.1f} us | dispatch timestamps, mean of the pass's last two launches |",
              f"| engine clock | {clock:.2f} GHz | GRBM_GUI_ACTIVE / {xcds} XCDs / kernel time |",
              f"| MFMA pipe busy | {100 * busy:.1f} % of SIMD cycles | SQ_VALU_MFMA_BUSY_CYCLES / ({simds} SIMDs x cycles) |",
-             f"| MFMA instructions x {per_mfma:,} FLOP | {mfma_flop / 1e9:.1f} GFLOP | SQ_INSTS_MFMA; algorithmic FLOP {flop / 1e9:.1f} G "
+             f"| FLOP of the MFMAs | {mfma_flop / 1e9:.1f} GFLOP | SQ_INSTS_VALU_MFMA_MOPS_BF16 x {MOP_FLOP}; algorithmic FLOP {flop / 1e9:.1f} G "
              f"(masked keys of diagonal blocks and padded decode heads are executed too) |",
              f"| MFMA rate at the run's clock | {mfma_flop / (us * 1e-6) / 1e12:.0f} TFLOP/s | executed MFMA FLOP / kernel time |",
              f"| algorithmic rate | {flop / (us * 1e-6) / 1e12:.0f} TFLOP/s = {100 * flop / (us * 1e-6) / 2.5e15:.1f} % of the 2.5 PFLOP/s bf16 peak | |",
