@@ -422,10 +422,11 @@ __device__ __forceinline__ void prefill_tile(const StepArgs& a, const WorkItem& 
 // run, as vector and matrix instructions share the SIMD's issue), and the chip clocks
 // at 2.1 GHz under this load.
 //
-// Measured on one 16,384-position chunk behind 8,616 cached ones, 16/2 heads: 1,816 us
-// against 1,962 us for the same tile with all waves in step (which left the overlap to
-// chance). Also measured: reading V and K in the matrix half only, 2,000 us; 32x32x16
-// MFMAs on this schedule, 1,990 us.
+// Measured on one 16,384-position chunk behind 8,616 cached ones, 16/2 heads: with the
+// page write 2,030 -> 1,877 us, in turn on one card with the same tile with all waves in
+// step (which left the overlap to chance); the kernel alone 1,790-1,830 us on a warm
+// card. Also measured, where it took 1,816 us: reading V and K in the matrix half only,
+// 2,000 us; 32x32x16 MFMAs on this schedule, 1,990 us.
 //
 // LDS holds the pages of a block one by one, 4 KB of K and 4 KB of V, so a transfer
 // copies 1 KB of one page, its page id and base are scalar, and the waits count LDS

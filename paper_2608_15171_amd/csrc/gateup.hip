@@ -24,9 +24,10 @@
 // operand fragment (16 rows x 64 bytes) is one conflict-free ds_read_b128.
 // The stream of transfers runs on into the workgroup's next tile, so a tile's
 // epilogue overlaps the next tile's loads.
-//   16,384 x 2,048 x 22,016: 1,252 -> 1,037 us (1.43 PFLOP/s; before: 32x32x16
-//   MFMAs, one barrier and one drain of the transfers per stage)
-//   16,384 x 11,008 x 2,048: 620 -> 490 us (1.51 PFLOP/s)
+//   16,384 tokens, the MLP's two projections: 1,948 -> 1,640 us in turn on one card
+//   (before: 32x32x16 MFMAs, one barrier and one drain of the transfers per stage);
+//   2,048 x 22,016 alone 1,052-1,100 us (1.34-1.40 PFLOP/s), 11,008 x 2,048 489-511
+//   us (1.45-1.51 PFLOP/s)
 // (transfers issued after the operand reads 1-2 % slower, one of two among the
 // MFMAs 4 %, both 8 %; 32x32x16 MFMAs in the same schedule 6-8 %)
 //
@@ -556,11 +557,11 @@ __global__ __launch_bounds__(kThreads, 1) void gateup_kernel(GemmArgs a) {
 // registers take twice the time: adjacent lanes then read different rows, and the
 // address unit takes one lane per clock instead of four. Eight waves measured
 // 0-10 % slower than four.) At the end the waves' sums meet in LDS and are added
-// in order. Against the tile kernels with a split reduction and its reducing
-// launch: 24 tokens x 2,048 x 22,016 with the activation 28.0 -> 20.9 us (4.3 TB/s
-// of weights), 11,008 x 2,048 22.0 -> 15.4 us (X, read by every workgroup, bounds
-// it), 2,048 x 2,048 kernel time 12.5 -> 4.3 us; 1 token 25.4 -> 22.3, 20.5 ->
-// 11.3, 10.6 -> 4.0 us.
+// in order. Against one tile kernel with a split reduction and its reducing launch,
+// calls one after another, weights from memory: 24 tokens x 2,048 x 22,016 with the
+// activation 28.4 -> 22.7 us (4.0 TB/s of weights), 11,008 x 2,048 24.6 -> 17.5 us (X,
+// read by every workgroup, bounds it), 2,048 x 2,048 11.8 -> 8.6 us, of which 4.3 are
+// the kernel's (12.5 before); 1 token 25.7 -> 21.5, 22.7 -> 13.4, 10.9 -> 8.4 us.
 constexpr int kRowsWaves = 4;
 
 template <int XT, int G, int WR, bool kAct>
