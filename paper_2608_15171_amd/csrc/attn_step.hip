@@ -424,7 +424,7 @@ __device__ __forceinline__ void prefill_tile(const StepArgs& a, const WorkItem& 
 //
 // Measured on one 16,384-position chunk behind 8,616 cached ones, 16/2 heads: with the
 // page write 2,030 -> 1,877 us, in turn on one card with the same tile with all waves in
-// step (which left the overlap to chance); the kernel alone 1,790-1,830 us on a warm
+// step (which left the overlap to chance); the kernel alone 1,790-1,870 us by
 // card. Also measured, where it took 1,816 us: reading V and K in the matrix half only,
 // 2,000 us; 32x32x16 MFMAs on this schedule, 1,990 us.
 //
