@@ -932,14 +932,16 @@ GateupChoice gateup_choose(int32_t T, int32_t H, int32_t N2, bool act, bool alig
   // and the others sum by blocks of four stages where eight would be longer.
   const int longest = (H / kBK + max_splits - 1) / max_splits;
   Shape best;
-  for (int bm : {256, 128, 64})
+  for (int bm : {256, 128, 64}) {
+    if (bm > kTailBM && T < bm) continue;   // no tile of that height
     for (int s = 1; s <= max_splits; ++s) {
-      if (bm == 256 && T >= 256 && s < max_splits) continue;
-      if (narrow && ((s > 1 && s * 4 * kBK != H) || (bm == 256 && T >= 256))) continue;
+      if (bm == 256 && s < max_splits) continue;
+      if (narrow && ((s > 1 && s * 4 * kBK != H) || bm == 256)) continue;
       const Shape c = shape_cost(T, H, N2, grid_max, bm, s);
       if (c.items > INT32_MAX / 2) continue;
       if (best.bm == 0 || c.cost < best.cost) best = c;
     }
+  }
   if (best.bm == 0) return r;
   r.kernel = GateupChoice::kTiles;
   r.rows = best.bm;

@@ -380,6 +380,7 @@ def test_gateup_choice_query():
                 assert none["splits"] == 1 and 1 <= full["splits"] <= most, (T, H, N)
                 assert aligned or full["splits"] == most
                 if full["kernel"] == "tiles":
+                    assert (full["rows"] == 64) == (full["main_tiles"] == 0)      # no height without a tile of it
                     assert full["main_tiles"] * full["rows"] + 64 * full["small_tiles"] >= T
                     assert full["main_tiles"] * full["rows"] + 64 * (full["small_tiles"] - 1) < T
 
