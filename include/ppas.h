@@ -377,8 +377,8 @@ size_t ppas_gateup_act_workspace_bytes(int32_t n_tokens, int32_t hidden, int32_t
  * kernel that ppas_gateup_proj, or with `activation` ppas_gateup_act (n_out = 2
  * n_inter), takes for this shape and workspace size on a device of num_cus compute
  * units (0 = 256), `aligned` if x and w are. Writes 8 int32 to `choice`: kernel (0
- * tiles, 1 few rows, 2 general), token rows of a main tile or few-row workgroup,
- * main tiles and 64-row tiles along the tokens, weight-row tiles of a few-row
+ * tiles, 1 few rows, 2 general), token rows of a main tile (64: none, 64-row tiles
+ * only) or few-row workgroup, main tiles and 64-row tiles along the tokens, weight-row tiles of a few-row
  * workgroup and their rows, reduction splits, 64-feature stages whose sum is added
  * to the total at a time (main tiles of 256 rows and the general kernel keep one
  * chain per split instead). PPAS_EINVAL for n_tokens == 0.

@@ -38,7 +38,7 @@ hipError_t launch_attn_step(const uint16_t* q, uint16_t* out, const uint16_t* kp
 struct GateupChoice {
   enum Kernel { kTiles = 0, kRows = 1, kGeneral = 2 };
   Kernel kernel = kGeneral;
-  int32_t rows = 256;                       // token rows of a main tile, or of a few-row workgroup
+  int32_t rows = 256;                       // token rows of a main tile (64: none), or of a few-row workgroup
   int32_t g = 0, wr = 0;                    // few rows: weight-row tiles per workgroup and their rows
   int32_t splits = 1;
   int32_t main_m = 0, tail_m = 0;           // tiles: main ones along the token rows, 64-row ones after them
